@@ -422,6 +422,9 @@ PTYCHO_API int ptycho_fft2(int32_t n, int32_t count, float *data_dev, int32_t di
  * every later launch of the selected classes (each pair adds a few
  * microseconds to the stream, so time a whole run with few classes);
  * 0 stops recording.  PTYCHO_E_INVALID for bits beyond class 7.
+ * Small far-field frames whose three passes run as one kernel count it as
+ * class 2 (projections) or class 1 (read-only passes); the other passes then
+ * record empty intervals.
  * ptycho_plan_timing_read waits for the last recorded event and returns the
  * summed milliseconds and the launch count of one class since timing was
  * last enabled. */

@@ -199,6 +199,11 @@ __device__ __forceinline__ constexpr int elem_index(int t, int e) {
     constexpr int T = N / E;
     return t + (e / R) * T + (e % R) * (N / R);
 }
+// The compile-time part of elem_index (the rest is t).
+template <int N, int E, int R>
+__device__ __forceinline__ constexpr int elem_const(int e) {
+    return (e / R) * (N / E) + (e % R) * (N / R);
+}
 template <int N, int E, int DIR>
 __device__ __forceinline__ int in_index(int t, int e) { return elem_index<N, E, FirstRadix<N, E, DIR>::value>(t, e); }
 template <int N, int E, int DIR>
@@ -230,8 +235,9 @@ __device__ __forceinline__ void twiddle_squares(int m_of_table, float2 *w) {
 }
 
 // All passes of one length-N transform held by thread t (0 <= t < N/E).
-// `Lds` provides ld(idx), st(idx, v) and sync() for this transform's
-// private N-element exchange buffer.
+// `Lds` provides ld(i, c), st(i, c, v) and sync() for this transform's
+// private N-element exchange buffer; the index is i + c, c known at compile
+// time and (in the first two passes) without bits in common with i.
 template <int N, int E, int DIR, int P, int L, class Lds>
 __device__ __forceinline__ void fft_pass(float2 *u, int t, Lds &lds) {
     using C = FftCfg<N, E>;
@@ -239,9 +245,8 @@ __device__ __forceinline__ void fft_pass(float2 *u, int t, Lds &lds) {
     if constexpr (P > 0) {
 #pragma unroll
         for (int b = 0; b < E / R; ++b) {
-            const int i = t + b * T;
 #pragma unroll
-            for (int r = 0; r < R; ++r) u[b * R + r] = lds.ld(i + r * (N / R));
+            for (int r = 0; r < R; ++r) u[b * R + r] = lds.ld(t, b * T + r * (N / R));
         }
     }
 #pragma unroll
@@ -265,7 +270,10 @@ __device__ __forceinline__ void fft_pass(float2 *u, int t, Lds &lds) {
             const int k = i & (L - 1);
             const int j = (i - k) * R + k;
 #pragma unroll
-            for (int r = 0; r < R; ++r) lds.st(j + r * L, u[b * R + r]);
+            for (int r = 0; r < R; ++r) {
+                if constexpr (L == 1) lds.st(t * R, b * T * R + r, u[b * R + r]);
+                else lds.st(j, r * L, u[b * R + r]);
+            }
         }
         lds.sync();
         fft_pass<N, E, DIR, P + 1, L * R>(u, t, lds);
@@ -289,9 +297,8 @@ __device__ __forceinline__ void fftk_pass(float2 (&u)[K][E], int t, Lds *lds) {
         for (int k = 0; k < K; ++k)
 #pragma unroll
             for (int b = 0; b < E / R; ++b) {
-                const int i = t + b * T;
 #pragma unroll
-                for (int r = 0; r < R; ++r) u[k][b * R + r] = lds[k].ld(i + r * (N / R));
+                for (int r = 0; r < R; ++r) u[k][b * R + r] = lds[k].ld(t, b * T + r * (N / R));
             }
     }
 #pragma unroll
@@ -318,7 +325,7 @@ __device__ __forceinline__ void fftk_pass(float2 (&u)[K][E], int t, Lds *lds) {
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int r = 0; r < R; ++r) lds[k].st(j + r * L, u[k][b * R + r]);
+                for (int r = 0; r < R; ++r) lds[k].st(j, r * L, u[k][b * R + r]);
         }
         lds[0].sync();
         fftk_pass<N, E, DIR, P + 1, L * R, K>(u, t, lds);
@@ -338,6 +345,8 @@ struct RowLds {
     __device__ __forceinline__ RowLds(float2 *lds, int row) : base(lds + row * (N + N / 16)) {}
     __device__ __forceinline__ float2 ld(int x) const { return base[x + (x >> 4)]; }
     __device__ __forceinline__ void st(int x, float2 v) { base[x + (x >> 4)] = v; }
+    __device__ __forceinline__ float2 ld(int i, int c) const { return ld(i + c); }
+    __device__ __forceinline__ void st(int i, int c, float2 v) { st(i + c, v); }
     __device__ __forceinline__ void sync() const { __syncthreads(); }
     static constexpr int floats2_per_row = N + N / 16;
 };
@@ -359,6 +368,8 @@ struct ColLds {
     }
     __device__ __forceinline__ float2 ld(int y) const { return base[row(y) * CB]; }
     __device__ __forceinline__ void st(int y, float2 v) { base[row(y) * CB] = v; }
+    __device__ __forceinline__ float2 ld(int i, int c) const { return ld(i + c); }
+    __device__ __forceinline__ void st(int i, int c, float2 v) { st(i + c, v); }
     __device__ __forceinline__ void sync() const { __syncthreads(); }
     static constexpr int floats2 = N * CB;
 };

@@ -6,6 +6,7 @@
 
 #include "plan.hpp"
 #include "stack_kernels.hpp"
+#include "frame_kernels.hpp"
 
 namespace ptycho {
 
@@ -63,6 +64,56 @@ static void launch_rows_inv(const StackArgs &a, bool wq, hipStream_t s) {
     else hipLaunchKernelGGL((k_rows_inv<N, K, MODE, false, NF, false>), grid, block, 0, s, a);
 }
 
+// Small far-field frames: the whole frame in one kernel.
+// Sizes of k_frame and k_frame_read: every mode count up to 64 points; at 128
+// points the projections of up to two modes (the registers of a 1024-thread
+// block hold no more; the line search there needs the kept row transforms).
+template <int N, int K>
+constexpr bool has_frame() { return N == 32 || N == 64 || (N == 128 && K <= 2); }
+template <int N>
+constexpr bool has_frame_read() { return N == 32 || N == 64; }
+
+// Whether the plan's projections take a frame per block rather than three
+// passes of blocks over all frames.  A block's frame takes a fixed time, so the
+// frames of a launch have to fill the chip's 256 CUs by half (DM cycle without
+// updates, us, three passes / frame per block: 64^2 x 3 modes 17 / 23 at 64
+// frames, 32 / 25 at 200, 216 / 145 at 1500; 128^2 x 1 mode 18 / 29 at 64,
+// 50 / 31 at 200, 290 / 183 at 1500; 128^2 x 2 modes 552 / 335 at 1500); one
+// mode up to 64 points is as fast or faster at any count (13 / 13 at 8 frames,
+// 80 / 43 at 1500).
+template <int N, int K>
+static bool by_frame(const ptycho_plan_s *p, const float2 *keep) {
+    if constexpr (!has_frame<N, K>()) return false;
+    if (N == 128 && keep != nullptr) return false;
+    return (N <= 64 && K == 1) || p->L.S >= 128;
+}
+
+template <int N, int K>
+static dim3 frame_blocks(int sn) {
+    return dim3((unsigned)((sn + FrameGeom<N, K>::FPB - 1) / FrameGeom<N, K>::FPB));
+}
+template <int N, int K, int OP, bool SUB>
+static void launch_frame_sub(const StackArgs &a, hipStream_t s) {
+    const size_t lds = sizeof(float2) * FrameGeom<N, K>::LDS_F2;
+    static const hipError_t attr = set_dyn_lds(k_frame<N, K, OP, SUB>, lds);
+    (void)attr;
+    const dim3 grid = frame_blocks<N, K>(a.S), block(FrameGeom<N, K>::THREADS);
+    hipLaunchKernelGGL((k_frame<N, K, OP, SUB>), grid, block, lds, s, a);
+}
+template <int N, int K, int OP>
+static void launch_frame(const StackArgs &a, hipStream_t s) {
+    if (a.frac != nullptr) launch_frame_sub<N, K, OP, true>(a, s);
+    else launch_frame_sub<N, K, OP, false>(a, s);
+}
+template <int N, int K, int OP, bool SUB>
+static void launch_frame_read(const StackArgs &a, hipStream_t s) {
+    const size_t lds = sizeof(float2) * FrameGeom<N, K>::LDS_F2;
+    static const hipError_t attr = set_dyn_lds(k_frame_read<N, K, OP, SUB>, lds);
+    (void)attr;
+    const dim3 grid = frame_blocks<N, K>(a.S), block(FrameGeom<N, K>::THREADS);
+    hipLaunchKernelGGL((k_frame_read<N, K, OP, SUB>), grid, block, lds, s, a);
+}
+
 // One pass over all stacks: forward rows, column op, inverse rows and the
 // per-stack gathers.  kind: 0 = AP projection, 1 = DM, 2 = ML gradient.
 // Exit waves go to `psi` (all frames) when it is given, else stay in the
@@ -91,29 +142,43 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         if (upd_bg) a.s2 = p->s2;
         if (keep) a.fwd = keep + (size_t)s0 * K * N * N;
         a.colin = a.fwd;
-        const dim3 rg(rows_blocks<N>(sn), p->d.n_modes);
-        {
-            Timed tm(p, TC_ROWS_FWD);
-            if (kind == 1) launch_rows_fwd<N, IN_DM, NF>(a, rg, s);
-            else launch_rows_fwd<N, IN_PHI, NF>(a, rg, s);
-        }
-        {
-            Timed tm(p, TC_COLS);
-            if (kind == 2) launch_cols_joint<N, K, OP_GRAD, NF>(a, s);
-            else if (kind == 1) launch_cols_joint<N, K, OP_CORR, NF>(a, s);
-            else launch_cols_joint<N, K, OP_PROJECT, NF>(a, s);
+        const bool whole = !NF && by_frame<N, K>(p, keep);
+        if (whole) {
+            if constexpr (has_frame<N, K>() && !NF) {
+                if (!wq) a.qbuf = nullptr;
+                // one kernel for the three passes: its time counts as the last one's
+                { Timed tm(p, TC_ROWS_FWD); }
+                { Timed tm(p, TC_COLS); }
+                Timed tm(p, TC_ROWS_INV);
+                if (kind == 2) launch_frame<N, K, OP_GRAD>(a, s);
+                else if (kind == 1) launch_frame<N, K, OP_CORR>(a, s);
+                else launch_frame<N, K, OP_PROJECT>(a, s);
+            }
+        } else {
+            const dim3 rg(rows_blocks<N>(sn), p->d.n_modes);
+            {
+                Timed tm(p, TC_ROWS_FWD);
+                if (kind == 1) launch_rows_fwd<N, IN_DM, NF>(a, rg, s);
+                else launch_rows_fwd<N, IN_PHI, NF>(a, rg, s);
+            }
+            {
+                Timed tm(p, TC_COLS);
+                if (kind == 2) launch_cols_joint<N, K, OP_GRAD, NF>(a, s);
+                else if (kind == 1) launch_cols_joint<N, K, OP_CORR, NF>(a, s);
+                else launch_cols_joint<N, K, OP_PROJECT, NF>(a, s);
+            }
+            {
+                Timed tm(p, TC_ROWS_INV);
+                if (kind == 1) launch_rows_inv<N, K, OUT_DM, NF>(a, wq, s);
+                else if (store) launch_rows_inv<N, K, OUT_STORE, NF>(a, wq, s);
+                else if (acc & ACC_PROBE) launch_rows_inv<N, K, OUT_SCR, NF>(a, wq, s);
+                else launch_rows_inv<N, K, OUT_NONE, NF>(a, wq, s);
+            }
         }
         if (upd_bg) {
             Timed tm(p, TC_OTHER);
             const int st = launch_bg_accum(p, sn, sidx == 0 ? 1 : 0);
             if (st) return st;
-        }
-        {
-            Timed tm(p, TC_ROWS_INV);
-            if (kind == 1) launch_rows_inv<N, K, OUT_DM, NF>(a, wq, s);
-            else if (store) launch_rows_inv<N, K, OUT_STORE, NF>(a, wq, s);
-            else if (acc & ACC_PROBE) launch_rows_inv<N, K, OUT_SCR, NF>(a, wq, s);
-            else launch_rows_inv<N, K, OUT_NONE, NF>(a, wq, s);
         }
         LAUNCHCHK();
         int st = PTYCHO_OK;
@@ -173,11 +238,46 @@ static int forward_pass_op(ptycho_plan_s *p, const float *obj, const float *prob
     return PTYCHO_OK;
 }
 
+// The same on small far-field frames: one launch over all frames (a block per
+// frame, no scratch).
+template <int N, int OP>
+static int frame_pass_op(ptycho_plan_s *p, const float *obj, const float *probe, const float *dobj,
+                         const float *dprobe, float *icalc, int llk_model) {
+    StackArgs a = stack_args(p, 0, p->d.n_frames, obj, probe);
+    a.dobj = (const float2 *)dobj;
+    a.dprobe = (const float2 *)dprobe;
+    a.icalc = icalc;
+    a.llk_model = llk_model;
+    a.red = p->red;
+    { Timed tm(p, TC_ROWS_FWD); }
+    Timed tm(p, TC_COLS);
+    return with_k(p->d.n_modes, [&](auto kk) {
+        constexpr int K = decltype(kk)::value;
+        if (a.frac != nullptr) launch_frame_read<N, K, OP, true>(a, p->stream);
+        else launch_frame_read<N, K, OP, false>(a, p->stream);
+        LAUNCHCHK();
+        return (int)PTYCHO_OK;
+    });
+}
+
 template <int N>
 static int forward_pass_n(ptycho_plan_s *p, int op, const float *obj, const float *probe, const float *dobj,
                           const float *dprobe, float *icalc, int llk_model, const float2 *keep) {
     return with_nf(p, [&](auto nf) {
         constexpr bool NF = decltype(nf)::value;
+        if constexpr (has_frame_read<N>() && !NF) {
+            switch (op) {
+                case OP_LLK: return frame_pass_op<N, OP_LLK>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+                case OP_ICALC: return frame_pass_op<N, OP_ICALC>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+                case OP_LS: return frame_pass_op<N, OP_LS>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+                case OP_LS2:
+                    // the gradient pass of the same plan kept no row transforms
+                    if (with_k(p->d.n_modes, [&](auto kk) { return (int)by_frame<N, decltype(kk)::value>(p, keep); }))
+                        return frame_pass_op<N, OP_LS>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+                    return forward_pass_op<N, OP_LS2, NF>(p, obj, probe, dobj, dprobe, icalc, llk_model, keep);
+                default: return fail(PTYCHO_E_INVALID, "internal: unknown forward op");
+            }
+        } else
         switch (op) {
             case OP_LLK: return forward_pass_op<N, OP_LLK, NF>(p, obj, probe, dobj, dprobe, icalc, llk_model, keep);
             case OP_ICALC: return forward_pass_op<N, OP_ICALC, NF>(p, obj, probe, dobj, dprobe, icalc, llk_model, keep);
