@@ -507,18 +507,28 @@ struct ObjTileArgs {
     float *denO;
     float2 *pnum;                 // partial sums [slot][OTILE_Y * OTILE_X]
     float *pden;
+    float *bmax;                  // one stack: the sums are written, not added to, and each block's
+                                  // denominator maximum goes here; null: several stacks
     const int2 *offs;             // sub-pixel windows: frame corners by frame (entry .w) ...
     const float2 *frac;           // ... and their fractions, or null (integer windows: entries)
 };
 
+// PY pixels (rows) per thread: 4, or 1 with four blocks (blockIdx.y) per tile
+// where the blocks are few.  The kernel is bound by the latency of a frame's
+// loads (a table entry, then the values), so a thread keeps 16 pixels' loads in
+// flight either way: 100 frames of 64^2 (80 blocks) 10.1 -> 5.5 us; sub-pixel
+// windows, 251 frames of 128^2, 107 -> 33 us (four values a pixel and one frame
+// at a time before).
+template <bool SUB, int PY>
 __global__ __launch_bounds__(256) void k_gather_obj(ObjTileArgs a) {
     const int tile = a.tiles[blockIdx.x];
     const int ty = tile / a.ntx, tx = tile % a.ntx;
-    const int col = threadIdx.x % OTILE_X, r0 = threadIdx.x / OTILE_X;
-    constexpr int RSTEP = 256 / OTILE_X;            // row phases per block
+    const int col = threadIdx.x % OTILE_X;
     const int px = tx * OTILE_X + col;
-    constexpr int PY = OTILE_Y / RSTEP;
-    constexpr int FU = 4;                            // frames per iteration
+    // the block's BY rows from rb on; a thread takes rows r0, r0 + RSTEP, ...
+    // (integer windows) or PY adjacent rows (sub-pixel windows)
+    constexpr int BY = 256 / OTILE_X * PY, RSTEP = SUB ? 1 : BY / PY;
+    const int r0 = blockIdx.y * BY + threadIdx.x / OTILE_X * (SUB ? PY : 1);
     float2 acc[PY];
     float den[PY];
 #pragma unroll
@@ -529,71 +539,96 @@ __global__ __launch_bounds__(256) void k_gather_obj(ObjTileArgs a) {
     const int N = a.N;
     const size_t fsz = (size_t)N * N;
     const int f0 = a.tptr[blockIdx.x], f1 = a.tptr[blockIdx.x + 1];
-    if (a.frac != nullptr) {
+    if constexpr (SUB) {
         // sub-pixel windows: object pixel (py, px) takes w_ab q(py - oy - a, px - ox - b) from every
         // frame, the adjoint of the bilinear view (the same weights), and w_ab sum_k |P_k|^2 at the
-        // same place for the denominator; the frame's corner comes from the device tables
-        for (int f = f0; f < f1; ++f) {
-            const int jf = a.tent[f].w;
-            const int2 o = a.offs[jf];
-            const float2 fr = a.frac[jf];
-            const float2 *qs = a.q + (size_t)a.tent[f].x * fsz;
-            const float wy[2] = {1.0f - fr.x, fr.x}, wx[2] = {1.0f - fr.y, fr.y};
+        // same place for the denominator; the frame's corner comes from the device tables.  A
+        // thread owns PY adjacent rows, which share their loads (PY + 1 rows of two columns instead
+        // of four values a pixel), for FS frames at a time; values outside the window are read
+        // clamped and replaced by 0.
+        constexpr int FS = PY == 1 ? 4 : 2;
+        for (int f = f0; f < f1; f += FS) {
+            int2 o[FS];
+            float2 fr[FS];
+            const float2 *qs[FS];
 #pragma unroll
-            for (int i = 0; i < PY; ++i) {
-                const int y = ty * OTILE_Y + r0 + RSTEP * i - o.x, x = px - o.y;
-#pragma unroll
-                for (int ay = 0; ay < 2; ++ay)
-#pragma unroll
-                    for (int bx = 0; bx < 2; ++bx) {
-                        const int yy = y - ay, xx = x - bx;
-                        if ((unsigned)yy < (unsigned)N && (unsigned)xx < (unsigned)N) {
-                            const float w = wy[ay] * wx[bx];
-                            const size_t pix = (size_t)yy * N + xx;
-                            const float2 v = qs[pix];
-                            acc[i].x += w * v.x;
-                            acc[i].y += w * v.y;
-                            den[i] += w * a.pint[pix];
-                        }
-                    }
+            for (int h = 0; h < FS; ++h) {
+                const int4 e = a.tent[min(f + h, f1 - 1)];
+                o[h] = a.offs[e.w];
+                fr[h] = a.frac[e.w];
+                qs[h] = a.q + (size_t)e.x * fsz;
             }
+            float2 v[FS][PY + 1];
+            float d[FS][PY + 1];
+#pragma unroll
+            for (int h = 0; h < FS; ++h) {
+                const int x = px - o[h].y, y0 = ty * OTILE_Y + r0 - o[h].x - 1;
+                const bool have = f + h < f1;
+                const bool in0 = have && (unsigned)x < (unsigned)N, in1 = have && (unsigned)(x - 1) < (unsigned)N;
+                const float w0 = 1.0f - fr[h].y, w1 = fr[h].y;
+                const int x0 = min(max(x, 0), N - 1), x1 = min(max(x - 1, 0), N - 1);
+#pragma unroll
+                for (int i = 0; i <= PY; ++i) {
+                    const int y = y0 + i;
+                    const size_t row = (size_t)min(max(y, 0), N - 1) * N;
+                    float2 va = qs[h][row + x0], vb = qs[h][row + x1];
+                    float da = a.pint[row + x0], db = a.pint[row + x1];
+                    const bool ya = in0 && (unsigned)y < (unsigned)N, yb = in1 && (unsigned)y < (unsigned)N;
+                    va = make_float2(ya ? va.x : 0.0f, ya ? va.y : 0.0f);
+                    vb = make_float2(yb ? vb.x : 0.0f, yb ? vb.y : 0.0f);
+                    da = ya ? da : 0.0f;
+                    db = yb ? db : 0.0f;
+                    v[h][i] = make_float2(w0 * va.x + w1 * vb.x, w0 * va.y + w1 * vb.y);
+                    d[h][i] = w0 * da + w1 * db;
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < FS; ++h)
+#pragma unroll
+                for (int i = 0; i < PY; ++i) {
+                    acc[i].x += (1.0f - fr[h].x) * v[h][i + 1].x + fr[h].x * v[h][i].x;
+                    acc[i].y += (1.0f - fr[h].x) * v[h][i + 1].y + fr[h].x * v[h][i].y;
+                    den[i] += (1.0f - fr[h].x) * d[h][i + 1] + fr[h].x * d[h][i];
+                }
         }
     } else {
-    // FU frames per iteration: all loads are issued before any is summed
-    // (the per-pixel order of the sum is unchanged).  Out-of-window pixels
-    // and missing frames read a clamped in-window address and are weighted
-    // 0, so the body is branch-free.
-    for (int f = f0; f < f1; f += FU) {
-        float2 v[FU][PY];
-        float d[FU][PY], m[FU][PY];
+        constexpr int FU = PY == 1 ? 16 : 4;
+        // FU frames per iteration: all loads are issued before any is summed
+        // (the per-pixel order of the sum is unchanged).  Out-of-window pixels
+        // and missing frames read a clamped in-window address and are weighted
+        // 0, so the body is branch-free.
+        for (int f = f0; f < f1; f += FU) {
+            float2 v[FU][PY];
+            float d[FU][PY], m[FU][PY];
 #pragma unroll
-        for (int h = 0; h < FU; ++h) {
-            const bool have = f + h < f1;
-            const int4 e = a.tent[have ? f + h : f];
-            const int x = px - e.z;
-            const bool xin = (unsigned)x < (unsigned)N && have;
-            const int xc = min(max(x, 0), N - 1);
-            const float2 *qs = a.q + (size_t)e.x * fsz;
+            for (int h = 0; h < FU; ++h) {
+                const bool have = f + h < f1;
+                const int4 e = a.tent[have ? f + h : f];
+                const int x = px - e.z;
+                const bool xin = (unsigned)x < (unsigned)N && have;
+                const int xc = min(max(x, 0), N - 1);
+                const float2 *qs = a.q + (size_t)e.x * fsz;
 #pragma unroll
-            for (int i = 0; i < PY; ++i) {
-                const int y = ty * OTILE_Y + r0 + RSTEP * i - e.y;
-                m[h][i] = (xin && (unsigned)y < (unsigned)N) ? 1.0f : 0.0f;
-                const size_t pix = (size_t)min(max(y, 0), N - 1) * N + xc;
-                v[h][i] = qs[pix];
-                d[h][i] = a.pint[pix];
+                for (int i = 0; i < PY; ++i) {
+                    const int y = ty * OTILE_Y + r0 + RSTEP * i - e.y;
+                    m[h][i] = (xin && (unsigned)y < (unsigned)N) ? 1.0f : 0.0f;
+                    const size_t pix = (size_t)min(max(y, 0), N - 1) * N + xc;
+                    v[h][i] = qs[pix];
+                    d[h][i] = a.pint[pix];
+                }
             }
+#pragma unroll
+            for (int h = 0; h < FU; ++h)
+#pragma unroll
+                for (int i = 0; i < PY; ++i) {
+                    acc[i].x += m[h][i] * v[h][i].x;
+                    acc[i].y += m[h][i] * v[h][i].y;
+                    den[i] += m[h][i] * d[h][i];
+                }
         }
-#pragma unroll
-        for (int h = 0; h < FU; ++h)
-#pragma unroll
-            for (int i = 0; i < PY; ++i) {
-                acc[i].x += m[h][i] * v[h][i].x;
-                acc[i].y += m[h][i] * v[h][i].y;
-                den[i] += m[h][i] * d[h][i];
-            }
-    }
     }
     const int slot = a.pslot[blockIdx.x];
+    float mx = 0.0f;
     if (slot >= 0) {
 #pragma unroll
         for (int i = 0; i < PY; ++i) {
@@ -601,21 +636,88 @@ __global__ __launch_bounds__(256) void k_gather_obj(ObjTileArgs a) {
             a.pnum[q] = acc[i];
             a.pden[q] = den[i];
         }
-        return;
-    }
-    if (px >= a.Nx) return;
+    } else if (px < a.Nx) {
 #pragma unroll
-    for (int i = 0; i < PY; ++i) {
-        const int py = ty * OTILE_Y + r0 + RSTEP * i;
-        if (py >= a.Ny) continue;
-        const size_t op = (size_t)py * a.Nx + px;
-        const float2 n0 = a.numO[op];
-        a.numO[op] = make_float2(n0.x + acc[i].x, n0.y + acc[i].y);
-        a.denO[op] += den[i];
+        for (int i = 0; i < PY; ++i) {
+            const int py = ty * OTILE_Y + r0 + RSTEP * i;
+            if (py >= a.Ny) continue;
+            const size_t op = (size_t)py * a.Nx + px;
+            if (a.bmax != nullptr) {
+                a.numO[op] = acc[i];
+                a.denO[op] = den[i];
+                mx = fmaxf(mx, den[i]);
+            } else {
+                const float2 n0 = a.numO[op];
+                a.numO[op] = make_float2(n0.x + acc[i].x, n0.y + acc[i].y);
+                a.denO[op] += den[i];
+            }
+        }
+    }
+    if (a.bmax != nullptr) {
+        mx = block_max(mx);
+        if (threadIdx.x == 0) a.bmax[blockIdx.y * gridDim.x + blockIdx.x] = mx;
     }
 }
 
-// Sums of the chunk partials of split tiles, added to the object sums: block
+// The object sums of a one-stack plan after k_gather_obj: the tiles of the
+// reduction list (count chunk partials from slot first on, added in order; 0
+// for a tile that no frame covers) are written, and part[block] receives the
+// denominators' maximum over those tiles and the gather's blocks.
+__global__ __launch_bounds__(256) void k_obj_finish(const int *rtile, const int *rfirst, const int *rcount, int nr,
+                                                    const float2 *pnum, const float *pden, float2 *numO, float *denO,
+                                                    int ntx, int Ny, int Nx, const float *bmax, int nb, float *part) {
+    constexpr int TP = OTILE_Y * OTILE_X, PX = TP / 256, U = 4;
+    float mx = 0.0f;
+    for (int b = blockIdx.x; b < nr; b += gridDim.x) {
+        const int tile = rtile[b], first = rfirst[b], n = rcount[b];
+        float2 s[PX];
+        float d[PX];
+#pragma unroll
+        for (int m = 0; m < PX; ++m) {
+            s[m] = make_float2(0.0f, 0.0f);
+            d[m] = 0.0f;
+        }
+        // U chunks' loads at a time; a missing chunk is read again and dropped
+        for (int c = 0; c < n; c += U) {
+            float2 v[U][PX];
+            float w[U][PX];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const size_t at = (size_t)(first + min(c + u, n - 1)) * TP + threadIdx.x;
+#pragma unroll
+                for (int m = 0; m < PX; ++m) {
+                    v[u][m] = pnum[at + m * 256];
+                    w[u][m] = pden[at + m * 256];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (c + u >= n) break;
+#pragma unroll
+                for (int m = 0; m < PX; ++m) {
+                    s[m] = cadd(s[m], v[u][m]);
+                    d[m] += w[u][m];
+                }
+            }
+        }
+        const int ty = tile / ntx, tx = tile % ntx;
+#pragma unroll
+        for (int m = 0; m < PX; ++m) {
+            const int q = threadIdx.x + m * 256;
+            const int py = ty * OTILE_Y + q / OTILE_X, px = tx * OTILE_X + q % OTILE_X;
+            if (py >= Ny || px >= Nx) continue;
+            const size_t op = (size_t)py * Nx + px;
+            numO[op] = s[m];
+            denO[op] = d[m];
+            mx = fmaxf(mx, d[m]);
+        }
+    }
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < nb; i += gridDim.x * 256) mx = fmaxf(mx, bmax[i]);
+    mx = block_max(mx);
+    if (threadIdx.x == 0) part[blockIdx.x] = mx;
+}
+
+// Several stacks: the chunk partials of split tiles, added to the object sums: block
 // b handles tile rtile[b] whose chunks occupy partial slots rfirst[b] ..
 // rfirst[b] + rcount[b] - 1.
 __global__ __launch_bounds__(256) void k_obj_chunk_reduce(const int *rtile, const int *rfirst, const int *rcount,
@@ -674,9 +776,16 @@ __global__ __launch_bounds__(256) void k_gather_probe(ProbeAllArgs a) {
 #pragma unroll
     for (int k = 0; k < K; ++k) acc[k] = make_float2(0.0f, 0.0f);
     float den = 0.0f;
+    // the next frame's table entries are read a frame ahead of its data
+    int jn = j0 < j1 ? a.order[a.q0 + j0] : 0;
+    int2 on = a.offs[jn];
     for (int q = j0; q < j1; ++q) {
-        const int j = a.order[a.q0 + q];
-        const int2 o = a.offs[j];
+        const int j = jn;
+        const int2 o = on;
+        if (q + 1 < j1) {
+            jn = a.order[a.q0 + q + 1];
+            on = a.offs[jn];
+        }
         const float2 ov = a.frac != nullptr ? view_at(a.obj, view_row(a.Ny, a.Nx, o, a.frac[j], y), x)
                                             : a.obj[(size_t)(o.x + y) * a.Nx + o.y + x];
         const float2 *ps = a.psi + (size_t)(FROM_SCR ? q : j) * K * fsz + vpix;
@@ -693,81 +802,128 @@ __global__ __launch_bounds__(256) void k_gather_probe(ProbeAllArgs a) {
     a.part_den[(size_t)c * fsz + idx] = den;
 }
 
-// numP, denP (=, or += with accumulate) the chunk partials in chunk order.
+// numP, denP (=, or += with accumulate) the sums of the C chunk partials in a
+// fixed order: G groups of threads take a contiguous part of the chunks each,
+// four loads in flight, and the groups' sums are added in order.  part[block]
+// receives the maximum of the block's denominators.  (One thread per value
+// walking all chunks, one load at a time, took 20 us for 4096 values in 32
+// chunks; 5 us this way.)
+template <int G>
 __global__ __launch_bounds__(256) void k_probe_reduce(const float2 *part_num, const float *part_den, int C, int K,
-                                                      long n2, float2 *numP, float *denP, int accumulate) {
+                                                      long n2, float2 *numP, float *denP, int accumulate,
+                                                      float *part) {
+    constexpr int W = 256 / G;                       // values per block and step
+    __shared__ float2 sn[G > 1 ? 256 : 1];
+    __shared__ float sd[G > 1 ? 256 : 1];
+    const int g = threadIdx.x / W, l = threadIdx.x % W;
+    const int c0 = g * C / G, c1 = (g + 1) * C / G;
     const long np = n2 * K;
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < np; i += (long)gridDim.x * 256) {
-        float2 s = accumulate ? numP[i] : make_float2(0.0f, 0.0f);
-        for (int c = 0; c < C; ++c) {
-            const float2 v = part_num[(size_t)c * np + i];
-            s.x += v.x;
-            s.y += v.y;
+    float mx = 0.0f;
+    for (long i0 = (long)blockIdx.x * W; i0 < np; i0 += (long)gridDim.x * W) {
+        const long i = i0 + l;
+        const bool in = i < np, dn = i < n2;
+        float2 s = make_float2(0.0f, 0.0f);
+        float d = 0.0f;
+        const long ic = in ? i : 0, id = dn ? i : 0;
+        for (int c = c0; c < c1; c += 4) {
+            float2 v[4];
+            float w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int cc = min(c + u, c1 - 1);
+                v[u] = part_num[(size_t)cc * np + ic];
+                w[u] = dn ? part_den[(size_t)cc * n2 + id] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (c + u >= c1) break;
+                s = cadd(s, v[u]);
+                d += w[u];
+            }
         }
-        numP[i] = s;
-        if (i < n2) {
-            float d = accumulate ? denP[i] : 0.0f;
-            for (int c = 0; c < C; ++c) d += part_den[(size_t)c * n2 + i];
-            denP[i] = d;
+        if constexpr (G > 1) {
+            sn[threadIdx.x] = s;
+            sd[threadIdx.x] = d;
+            __syncthreads();
+            if (g == 0) {
+#pragma unroll
+                for (int m = 1; m < G; ++m) {
+                    s = cadd(s, sn[m * W + l]);
+                    d += sd[m * W + l];
+                }
+            }
+            __syncthreads();
+        }
+        if (g == 0 && in) {
+            if (accumulate) s = cadd(numP[i], s);
+            numP[i] = s;
+            if (dn) {
+                if (accumulate) d += denP[i];
+                denP[i] = d;
+                mx = fmaxf(mx, d);
+            }
         }
     }
+    mx = block_max(mx);
+    if (threadIdx.x == 0) part[blockIdx.x] = mx;
 }
 
 // ====================================================== normalisation ===
-// Per-block maxima of the object and probe denominators.
-__global__ __launch_bounds__(256) void k_max_partial(const float *denO, long nO, const float *denP,
-                                                     long nP, float *part) {
-    float mo = 0.0f, mp = 0.0f;
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < nO; i += (long)gridDim.x * 256)
-        mo = fmaxf(mo, denO[i]);
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < nP; i += (long)gridDim.x * 256)
-        mp = fmaxf(mp, denP[i]);
-    mo = block_max(mo);
-    mp = block_max(mp);
-    if (threadIdx.x == 0) {
-        part[blockIdx.x] = mo;
-        part[gridDim.x + blockIdx.x] = mp;
+// Per-block maxima of the object denominators (plans of several stacks).
+__global__ __launch_bounds__(256) void k_max_partial(const float *den, long n, float *part) {
+    float m = 0.0f;
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) m = fmaxf(m, den[i]);
+    m = block_max(m);
+    if (threadIdx.x == 0) part[blockIdx.x] = m;
+}
+
+// The maximum of n partials, in every thread of the block.
+__device__ __forceinline__ float max_of_partials(const float *part, int n) {
+    float m = 0.0f;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) m = fmaxf(m, part[i]);
+    return block_max(m);
+}
+
+// O <- (numO + a O)/(denO + a), a = dO * max(denO).
+__global__ __launch_bounds__(256) void k_normalize_obj(float2 *obj, const float2 *numO, const float *denO, long nO,
+                                                       const float *part, int npart, float dO) {
+    const float ao = dO * max_of_partials(part, npart);
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < nO; i += (long)gridDim.x * 256) {
+        const float d = denO[i] + ao;
+        if (d > 0.0f) {
+            const float2 n = numO[i], o = obj[i];
+            const float r = 1.0f / d;
+            obj[i] = make_float2((n.x + ao * o.x) * r, (n.y + ao * o.y) * r);
+        }
     }
 }
 
-__device__ __forceinline__ void reduce_partials(const float *part, int npart, float &mo, float &mp) {
-    float a = 0.0f, b = 0.0f;
-    for (int i = threadIdx.x; i < npart; i += blockDim.x) {
-        a = fmaxf(a, part[i]);
-        b = fmaxf(b, part[npart + i]);
-    }
-    mo = block_max(a);
-    mp = block_max(b);
-}
-
-// O <- (numO + a O)/(denO + a), a = dO * max(denO); same for every probe mode.
-__global__ __launch_bounds__(256) void k_normalize(float2 *obj, const float2 *numO, const float *denO,
-                                                   long nO, float2 *probe, const float2 *numP,
-                                                   const float *denP, int n2, int K, const float *part,
-                                                   int npart, float dO, float dP, unsigned upd) {
-    float mo, mp;
-    reduce_partials(part, npart, mo, mp);
-    const float ao = dO * mo, ap = dP * mp;
-    if (upd & 1u) {
-        for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < nO; i += (long)gridDim.x * 256) {
-            const float d = denO[i] + ao;
-            if (d > 0.0f) {
-                const float2 n = numO[i], o = obj[i];
-                const float r = 1.0f / d;
-                obj[i] = make_float2((n.x + ao * o.x) * r, (n.y + ao * o.y) * r);
-            }
+// The same for every probe mode; pint receives sum_k |P_k|^2 of the new probe,
+// which the next cycle's object sums need.
+template <int K>
+__global__ __launch_bounds__(256) void k_normalize_probe(float2 *probe, const float2 *numP, const float *denP,
+                                                         int n2, const float *part, int npart, float dP,
+                                                         float *pint) {
+    const float ap = dP * max_of_partials(part, npart);
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n2; i += gridDim.x * 256) {
+        const float d = denP[i] + ap;
+        float2 n[K], p[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            n[k] = numP[(size_t)k * n2 + i];
+            p[k] = probe[(size_t)k * n2 + i];
         }
-    }
-    if (upd & 2u) {
-        const long np = (long)n2 * K;
-        for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < np; i += (long)gridDim.x * 256) {
-            const float d = denP[i % n2] + ap;
+        const float r = 1.0f / d;
+        float v = 0.0f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
             if (d > 0.0f) {
-                const float2 n = numP[i], p = probe[i];
-                const float r = 1.0f / d;
-                probe[i] = make_float2((n.x + ap * p.x) * r, (n.y + ap * p.y) * r);
+                p[k] = make_float2((n[k].x + ap * p[k].x) * r, (n[k].y + ap * p[k].y) * r);
+                probe[(size_t)k * n2 + i] = p[k];
             }
+            v += cnorm(p[k]);
         }
+        pint[i] = v;
     }
 }
 
@@ -795,13 +951,12 @@ __global__ __launch_bounds__(256) void k_psi_init(const float2 *obj, const float
     }
 }
 
-// Sum of `n` partials (fixed order, one block of SUM_THREADS) into out[0]
-// (+= if accumulate).  Each thread keeps four running sums over its
+// Sum of `n` partials in a fixed order by one block of SUM_THREADS threads
+// (the result in thread 0).  Each thread keeps four running sums over its
 // elements i = t + SUM_THREADS m, m = 0, 1, 2, 3 taken in turn, so that four
 // loads are in flight per thread; the order depends on n alone.
 constexpr int SUM_THREADS = 1024;
-__global__ __launch_bounds__(SUM_THREADS) void k_sum_partials(const double *red, long n, int stride, double *out,
-                                                              int accumulate) {
+__device__ __forceinline__ double sum_partials(const double *red, long n, int stride) {
     constexpr long T = SUM_THREADS;
     double v0 = 0.0, v1 = 0.0, v2 = 0.0, v3 = 0.0;
     long i = threadIdx.x;
@@ -812,8 +967,17 @@ __global__ __launch_bounds__(SUM_THREADS) void k_sum_partials(const double *red,
         v3 += red[(i + 3 * T) * stride];
     }
     for (; i < n; i += T) v0 += red[i * stride];
-    const double v = block_sum((v0 + v1) + (v2 + v3));
-    if (threadIdx.x == 0) out[0] = accumulate ? out[0] + v : v;
+    return block_sum((v0 + v1) + (v2 + v3));
+}
+// Block b: out[b] = the sum of red[b], red[b + stride], ... (n of them);
+// copy_from (if any) is copied to out[gridDim.x].
+__global__ __launch_bounds__(SUM_THREADS) void k_sum_partials(const double *red, long n, int stride, double *out,
+                                                              const double *copy_from) {
+    const double v = sum_partials(red + blockIdx.x, n, stride);
+    if (threadIdx.x == 0) {
+        out[blockIdx.x] = v;
+        if (copy_from != nullptr && blockIdx.x == 0) out[gridDim.x] = copy_from[0];
+    }
 }
 
 

@@ -22,15 +22,20 @@ enum {
     CG_GAMMA = 7,
     CG_NSCAL = 16
 };
-constexpr int CG_NPART = 256;   // blocks of the inner-product reduction
+constexpr int CG_NPART = 256;   // partials per product that the state has room for (layout only)
+constexpr int CG_BLOCKS = 1024; // most blocks of the inner-product reduction (partials in the workspace)
 
 __global__ void k_cg_reset(double *scal) {
     if (threadIdx.x < CG_NSCAL) scal[threadIdx.x] = 0.0;
 }
 
-__global__ __launch_bounds__(256) void k_scale_copy(float2 *dst, const float2 *src, long n, float s) {
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256)
-        dst[i] = cscale(src[i], s);
+// a_dst = s a_src and b_dst = s b_src.
+__global__ __launch_bounds__(256) void k_scale_copy(float2 *a_dst, const float2 *a_src, long na, float2 *b_dst,
+                                                    const float2 *b_src, long nb, float s) {
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < na + nb; i += (long)gridDim.x * 256) {
+        if (i < na) a_dst[i] = cscale(a_src[i], s);
+        else b_dst[i - na] = cscale(b_src[i - na], s);
+    }
 }
 
 // Partials of <gO,gO>, <gO,gO_prev>, <gP,gP>, <gP,gP_prev> with g = 2 * sums,
@@ -65,18 +70,21 @@ __global__ __launch_bounds__(256) void k_cg_dots(const float2 *sumO, const float
     }
 }
 
-// beta (Polak-Ribiere, clipped at 0) and the preconditioning scale s.
-__global__ __launch_bounds__(256) void k_cg_beta(const double *part, const float *maxpart, int nmax, double *scal,
-                                                 double *hist_slot) {
+// The LLK from its nred partials, beta (Polak-Ribiere, clipped at 0) and the
+// preconditioning scale s.
+__global__ __launch_bounds__(SUM_THREADS) void k_cg_beta(const double *red, long nred, const double *part, int npart,
+                                                         const float *maxO, int nmaxO, const float *maxP, int nmaxP,
+                                                         double *scal, double *hist_slot) {
+    const double llk = sum_partials(red, nred, 1);
     double a[4];
     for (int m = 0; m < 4; ++m) {
         double v = 0.0;
-        for (int i = threadIdx.x; i < CG_NPART; i += 256) v += part[4 * i + m];
+        for (int i = threadIdx.x; i < npart; i += SUM_THREADS) v += part[4 * i + m];
         a[m] = block_sum(v);
     }
-    float mo, mp;
-    reduce_partials(maxpart, nmax, mo, mp);
+    const float mo = max_of_partials(maxO, nmaxO), mp = max_of_partials(maxP, nmaxP);
     if (threadIdx.x == 0) {
+        scal[CG_LLK] = llk;
         const double s = mp > 0.0f ? (double)mo / (double)mp : 1.0;
         const double zg = a[0] + s * a[2];
         double beta = 0.0;
@@ -88,7 +96,7 @@ __global__ __launch_bounds__(256) void k_cg_beta(const double *part, const float
         scal[CG_S] = s;
         scal[CG_ZG] = zg;
         scal[CG_HAVE] = 1.0;
-        if (hist_slot) hist_slot[0] = scal[CG_LLK];
+        if (hist_slot) hist_slot[0] = llk;
     }
 }
 
@@ -122,9 +130,12 @@ __global__ __launch_bounds__(256) void k_cg_direction(const float2 *sumO, float2
     }
 }
 
-// x <- x + gamma d with gamma = -L'(0)/L''(0) (0 unless L''(0) > 0).
+// x <- x + gamma d with gamma = -L'(0)/L''(0) (0 unless L''(0) > 0); pint
+// receives sum_k |P_k|^2 of the new probe, which the next cycle's object sums
+// need.
+template <int K>
 __global__ __launch_bounds__(256) void k_cg_step(float2 *obj, const float2 *dO, long no, float2 *probe,
-                                                 const float2 *dP, long np, unsigned upd, double *scal) {
+                                                 const float2 *dP, int n2, unsigned upd, double *scal, float *pint) {
     const double l1 = scal[CG_L1], l2 = scal[CG_L2];
     const double gd = (l2 > 0.0 && isfinite(l1) && isfinite(l2)) ? -l1 / l2 : 0.0;
     const float gamma = (float)gd;
@@ -136,9 +147,21 @@ __global__ __launch_bounds__(256) void k_cg_step(float2 *obj, const float2 *dO, 
         }
     }
     if (upd & 2u) {
-        for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < np; i += (long)gridDim.x * 256) {
-            const float2 d = dP[i], p = probe[i];
-            probe[i] = make_float2(p.x + gamma * d.x, p.y + gamma * d.y);
+        for (int i = blockIdx.x * 256 + threadIdx.x; i < n2; i += gridDim.x * 256) {
+            float2 d[K], p[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                d[k] = dP[(size_t)k * n2 + i];
+                p[k] = probe[(size_t)k * n2 + i];
+            }
+            float v = 0.0f;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                p[k] = make_float2(p[k].x + gamma * d[k].x, p[k].y + gamma * d[k].y);
+                probe[(size_t)k * n2 + i] = p[k];
+                v += cnorm(p[k]);
+            }
+            pint[i] = v;
         }
     }
 }

@@ -130,7 +130,7 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
     const bool wq = (acc & ACC_OBJ) != 0;
     if (wq) {
         Timed tm(p, TC_OTHER);
-        const int st = launch_probe_intensity(p, probe);
+        const int st = need_probe_intensity(p, probe);
         if (st) return st;
     }
     for (int sidx = 0; sidx < p->L.nstacks; ++sidx) {
@@ -138,7 +138,7 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         StackArgs a = stack_args(p, s0, sn, obj, probe);
         a.psi = (const float2 *)psi;
         a.psi_out = (float2 *)psi;
-        a.red = p->red + (size_t)sidx * p->L.maxb;
+        a.red = p->red + p->red_n;
         if (upd_bg) a.s2 = p->s2;
         if (keep) a.fwd = keep + (size_t)s0 * K * N * N;
         a.colin = a.fwd;
@@ -146,6 +146,7 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         if (whole) {
             if constexpr (has_frame<N, K>() && !NF) {
                 if (!wq) a.qbuf = nullptr;
+                if (kind == 2) p->red_n += frame_blocks<N, K>(sn).x;
                 // one kernel for the three passes: its time counts as the last one's
                 { Timed tm(p, TC_ROWS_FWD); }
                 { Timed tm(p, TC_COLS); }
@@ -155,6 +156,7 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
                 else launch_frame<N, K, OP_PROJECT>(a, s);
             }
         } else {
+            if (kind == 2) p->red_n += cols_blocks<N>(sn);
             const dim3 rg(rows_blocks<N>(sn), p->d.n_modes);
             {
                 Timed tm(p, TC_ROWS_FWD);
@@ -185,7 +187,7 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         // ML position shifts from the gradient wave left in the scratch
         if (kind == 2 && p->shifts_in_grad) st = launch_ml_shifts(p, obj, probe, s0, sn);
         if (!st && (acc & ACC_OBJ)) st = object_sums(p, sidx);
-        if (!st && (acc & ACC_PROBE)) st = probe_sums(p, obj, p->scr, s0, sn, true, true);
+        if (!st && (acc & ACC_PROBE)) st = probe_sums(p, obj, p->scr, s0, sn, true, sidx > 0);
         if (st) return st;
     }
     return PTYCHO_OK;
@@ -211,7 +213,6 @@ static int forward_pass_op(ptycho_plan_s *p, const float *obj, const float *prob
     const int J = p->d.n_frames;
     const int S = (OP == OP_LS2) ? Lp.S_ls2 : ls ? Lp.S_ls : Lp.S;
     const int nst = (OP == OP_LS2) ? Lp.nstacks_ls2 : ls ? Lp.nstacks_ls : Lp.nstacks;
-    const int maxb = (OP == OP_LS2) ? Lp.maxb_ls2 : ls ? Lp.maxb_ls : Lp.maxb;
     hipStream_t s = p->stream;
     for (int sidx = 0; sidx < nst; ++sidx) {
         const int s0 = sidx * S, sn = std::min(S, J - s0);
@@ -220,7 +221,8 @@ static int forward_pass_op(ptycho_plan_s *p, const float *obj, const float *prob
         a.dprobe = (const float2 *)dprobe;
         a.icalc = icalc;
         a.llk_model = llk_model;
-        a.red = p->red + (size_t)sidx * maxb * (ls ? 2 : 1);
+        a.red = p->red + p->red_n * (ls ? 2 : 1);
+        p->red_n += cols_blocks<N>(sn);
         if (OP == OP_LS2) a.colin = keep + (size_t)s0 * p->d.n_modes * N * N;
         const dim3 rg(rows_blocks<N>(sn), p->d.n_modes);
         {
@@ -253,6 +255,7 @@ static int frame_pass_op(ptycho_plan_s *p, const float *obj, const float *probe,
     Timed tm(p, TC_COLS);
     return with_k(p->d.n_modes, [&](auto kk) {
         constexpr int K = decltype(kk)::value;
+        p->red_n = frame_blocks<N, K>(a.S).x;
         if (a.frac != nullptr) launch_frame_read<N, K, OP, true>(a, p->stream);
         else launch_frame_read<N, K, OP, false>(a, p->stream);
         LAUNCHCHK();

@@ -54,7 +54,7 @@ struct Layout {
     size_t nent_max, nfr_max, nred;
     size_t off_offs, off_order, off_lists, off_ent_fr, off_opart, off_scr, off_q, off_pint, off_numO, off_denO,
         off_numP, off_denP, off_pnum, off_pden, off_part, off_red, off_scal, off_s2, off_bsum, off_prop,
-        off_pspart, off_shift, off_pos, off_pos0, off_frac, total;
+        off_pspart, off_shift, off_pos, off_pos0, off_frac, off_bmax, off_cpart, total;
     int pos_chunks;               // row chunks per frame of the position-shift sums
 };
 
@@ -101,6 +101,14 @@ struct ptycho_plan_s {
     bool pos_ready = false;
     double pos_mult = 1.0, pos_min_grad = 0.1;
     bool shifts_in_grad = false; // the gradient pass also takes the ML position shifts
+    // within one call: whether pint holds the current probe's intensity, the
+    // reduction partials written so far (pairs for the line search), and the
+    // maximum partials of the object and probe denominators in part
+    bool pint_ready = false;
+    long red_n = 0;
+    int npartO = 0, npartP = 0;
+    float *bmax = nullptr;       // the object gather's block maxima (one-stack plans)
+    double *cpart = nullptr;     // inner-product partials of the CG cycle
     std::vector<float2> h_prop;
     std::vector<double> h_pos;   // host copies of the uploaded corners and fractions
     std::vector<float2> h_frac;
@@ -109,7 +117,8 @@ struct ptycho_plan_s {
     int ntx, nty;
     // Object-gather lists.  A list is a run of blocks (tile, entry range,
     // partial slot or -1) followed by a run of reductions (split tile, first
-    // slot, count), stored in h_lists; GatherList gives the offsets.
+    // slot, count; one-stack plans also list the uncovered tiles, count 0),
+    // stored in h_lists; GatherList gives the offsets.
     struct GatherList {
         int nb, blk_tile, blk_ptr, blk_slot, nr, red_tile, red_first, red_count;
     };
@@ -164,7 +173,7 @@ StackArgs stack_args(ptycho_plan_s *p, int s0, int sn, const float *obj, const f
 int object_sums(ptycho_plan_s *p, int sidx);
 int probe_sums(ptycho_plan_s *p, const float *obj, const float2 *psi, int q0, int nq, bool from_scr,
                bool accumulate);
-int launch_probe_intensity(ptycho_plan_s *p, const float *probe);
+int need_probe_intensity(ptycho_plan_s *p, const float *probe);
 int launch_bg_accum(ptycho_plan_s *p, int sn, int first);
 // ML position shifts of the stack's slots s0 .. s0+sn from the gradient wave
 // the inverse row pass left in the stack scratch.

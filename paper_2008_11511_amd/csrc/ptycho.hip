@@ -95,7 +95,8 @@ static int ensure_twiddles() {
     return PTYCHO_OK;
 }
 
-static constexpr int NPART = 512;       // blocks of the max-reduction
+static constexpr int NPART = 1024;      // most blocks of a max-reduction
+static constexpr int GATHER_SPLIT = 1024;   // object gathers of at most so many blocks run four per tile
 static constexpr int NSCAL = 64;        // device scalars
 static constexpr int SC_NOBS = 0;       //   unmasked pixels of all frames (double)
 
@@ -104,7 +105,7 @@ static constexpr int SC_NOBS = 0;       //   unmasked pixels of all frames (doub
 static int probe_chunks(const ptycho_desc_t &d) {
     const long blocks = (long)((d.n * d.n + 255) / 256);
     long c = (4096 + blocks - 1) / blocks;
-    c = std::max(1L, std::min(c, 32L));
+    c = std::max(1L, std::min(c, d.n <= 64 ? 64L : 32L));
     return (int)std::min<long>(c, d.n_frames);
 }
 
@@ -158,8 +159,9 @@ static Layout layout_for(const ptycho_desc_t &d) {
     // object-gather lists per stack: per block tile, entry range, partial
     // slot (plus one end pointer per list); per split tile: tile, first
     // slot, count
+    // (one stack also lists its uncovered tiles)
     const size_t nb_st = L.nent_max + L.nfr_max / 16 + L.nstacks;
-    L.nlist_ints = 3 * nb_st + 3 * L.nent_max + 2;
+    L.nlist_ints = 3 * nb_st + 3 * std::max(L.nent_max, (size_t)ntiles) + 2;
     L.npslots = std::min<size_t>(8192, L.nfr_max / 8 + 1);
     L.nred = std::max({(size_t)L.nstacks * L.maxb, (size_t)L.nstacks_ls * L.maxb_ls * 2,
                        (size_t)L.nstacks_ls2 * L.maxb_ls2 * 2});
@@ -199,6 +201,8 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.off_pos = o; o = up(o + (pst ? sizeof(double) * 2 * (size_t)J : 0));
     L.off_pos0 = o; o = up(o + (pst ? sizeof(double) * 2 * (size_t)J : 0));
     L.off_frac = o; o = up(o + (pst ? sizeof(float2) * (size_t)J : 0));
+    L.off_bmax = o; o = up(o + (L.nstacks == 1 ? sizeof(float) * (nb_st + 4 * GATHER_SPLIT) : 0));
+    L.off_cpart = o; o = up(o + sizeof(double) * 4 * CG_BLOCKS);
     L.total = o;
     return L;
 }
@@ -333,6 +337,17 @@ static int build_host_tables(ptycho_plan_s *p, const Layout &L, const int32_t *o
             if (nch > 1) slots += nch;
             ents.insert(ents.end(), v.begin(), v.end());
             v.clear();
+        }
+        if (L.nstacks == 1) {
+            // tiles that no frame covers: their sums are cleared
+            std::vector<char> covered(ntiles, 0);
+            for (int t : tiles) covered[t] = 1;
+            for (int t = 0; t < ntiles; ++t)
+                if (!covered[t]) {
+                    rt.push_back(t);
+                    rf.push_back(0);
+                    rc.push_back(0);
+                }
         }
         bp.push_back((int)(ents.size() - ent_base));
         max_slots = std::max(max_slots, slots);
@@ -494,6 +509,8 @@ extern "C" int ptycho_plan(const ptycho_desc_t *d, const int32_t *offsets, const
     p->part = (float *)(p->ws + L.off_part);
     p->red = (double *)(p->ws + L.off_red);
     p->scal = (double *)(p->ws + L.off_scal);
+    if (L.nstacks == 1) p->bmax = (float *)(p->ws + L.off_bmax);
+    p->cpart = (double *)(p->ws + L.off_cpart);
     if (d->flags & PTYCHO_FLAG_BACKGROUND) {
         p->s2 = (float *)(p->ws + L.off_s2);
         p->bsum = (double *)(p->ws + L.off_bsum);
@@ -710,10 +727,27 @@ int ptycho::object_sums(ptycho_plan_s *p, int sidx) {
     a.pden = p->opden;
     a.offs = p->offs;
     a.frac = p->pos_ready ? p->frac : nullptr;
+    a.bmax = p->bmax;
     Timed tm(p, TC_GATHER_OBJ);
-    hipLaunchKernelGGL(k_gather_obj, dim3(gl.nb), dim3(256), 0, p->stream, a);
-    if (gl.nr > 0) {
-        const int *L0 = p->lists;
+    // few blocks: each takes a quarter of a tile's rows, one pixel per thread
+    // and four times the frames in flight
+    const bool quarter = gl.nb <= GATHER_SPLIT;
+    const dim3 grid(gl.nb, quarter ? 4 : 1);
+    if (a.frac != nullptr) {
+        if (quarter) hipLaunchKernelGGL((k_gather_obj<true, 1>), grid, dim3(256), 0, p->stream, a);
+        else hipLaunchKernelGGL((k_gather_obj<true, 4>), grid, dim3(256), 0, p->stream, a);
+    } else {
+        if (quarter) hipLaunchKernelGGL((k_gather_obj<false, 1>), grid, dim3(256), 0, p->stream, a);
+        else hipLaunchKernelGGL((k_gather_obj<false, 4>), grid, dim3(256), 0, p->stream, a);
+    }
+    const int nmax = (int)(grid.x * grid.y);
+    const int *L0 = p->lists;
+    if (p->bmax) {
+        p->npartO = std::max(1, std::min(std::max(gl.nr, (nmax + 255) / 256), NPART));
+        hipLaunchKernelGGL(k_obj_finish, dim3(p->npartO), dim3(256), 0, p->stream, L0 + gl.red_tile,
+                           L0 + gl.red_first, L0 + gl.red_count, gl.nr, p->opnum, p->opden, p->numO, p->denO, p->ntx,
+                           p->d.obj_ny, p->d.obj_nx, p->bmax, nmax, p->part);
+    } else if (gl.nr > 0) {
         hipLaunchKernelGGL(k_obj_chunk_reduce, dim3(gl.nr), dim3(256), 0, p->stream, L0 + gl.red_tile,
                            L0 + gl.red_first, L0 + gl.red_count, p->opnum, p->opden, p->numO, p->denO, p->ntx,
                            p->d.obj_ny, p->d.obj_nx);
@@ -752,32 +786,45 @@ int ptycho::probe_sums(ptycho_plan_s *p, const float *obj, const float2 *psi, in
         else hipLaunchKernelGGL((k_gather_probe<K, false>), grid, dim3(256), 0, p->stream, a);
         return (int)PTYCHO_OK;
     });
-    hipLaunchKernelGGL(k_probe_reduce, dim3(grid_for(n2 * a.K)), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
-                       a.K, n2, p->numP, p->denP, accumulate ? 1 : 0);
+    // chunk groups side by side where there are many chunks of few values
+    const int G = chunks >= 8 ? 4 : 1;
+    p->npartP = (int)std::max(1L, std::min((n2 * a.K * G + 255) / 256, (long)NPART));
+    if (G == 4)
+        hipLaunchKernelGGL((k_probe_reduce<4>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
+                           a.K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
+    else
+        hipLaunchKernelGGL((k_probe_reduce<1>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
+                           a.K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
     LAUNCHCHK();
     return PTYCHO_OK;
 }
 
-static int zero_sums(ptycho_plan_s *p, unsigned acc) {
-    const size_t no = (size_t)p->d.obj_ny * p->d.obj_nx, n2 = (size_t)p->d.n * p->d.n;
-    int st = PTYCHO_OK;
-    if (acc & ACC_OBJ) {
-        st = zero_async(p->numO, up(sizeof(float2) * no), p->stream);
-        if (!st) st = zero_async(p->denO, up(sizeof(float) * no), p->stream);
-    }
-    if (!st && (acc & ACC_PROBE)) {
-        st = zero_async(p->numP, up(sizeof(float2) * p->d.n_modes * n2), p->stream);
-        if (!st) st = zero_async(p->denP, up(sizeof(float) * n2), p->stream);
-    }
-    return st;
+// Clears the object sums where stacks add to them (one stack writes them).
+static int zero_object_sums(ptycho_plan_s *p) {
+    if (p->bmax) return PTYCHO_OK;
+    const size_t no = (size_t)p->d.obj_ny * p->d.obj_nx;
+    const int st = zero_async(p->numO, up(sizeof(float2) * no), p->stream);
+    return st ? st : zero_async(p->denO, up(sizeof(float) * no), p->stream);
 }
 
-// Probe intensity image sum_k |P_k|^2 (the object denominator's term).
-int ptycho::launch_probe_intensity(ptycho_plan_s *p, const float *probe) {
+// The maximum partials of the object denominators where the gather did not
+// leave them (several stacks).
+static void max_object_sums(ptycho_plan_s *p) {
+    if (p->bmax) return;
+    const long no = (long)p->d.obj_ny * p->d.obj_nx;
+    p->npartO = 512;
+    hipLaunchKernelGGL(k_max_partial, dim3(p->npartO), dim3(256), 0, p->stream, p->denO, no, p->part);
+}
+
+// Probe intensity image sum_k |P_k|^2 (the object denominator's term), unless
+// an earlier cycle of the call left that of the current probe.
+int ptycho::need_probe_intensity(ptycho_plan_s *p, const float *probe) {
+    if (p->pint_ready) return PTYCHO_OK;
     const long n2 = (long)p->d.n * p->d.n;
     hipLaunchKernelGGL(k_probe_intensity, dim3(grid_for(n2)), dim3(256), 0, p->stream, (const float2 *)probe,
                        p->d.n_modes, n2, p->pint);
     LAUNCHCHK();
+    p->pint_ready = true;
     return PTYCHO_OK;
 }
 
@@ -789,17 +836,33 @@ int ptycho::launch_bg_accum(ptycho_plan_s *p, int sn, int first) {
     return PTYCHO_OK;
 }
 
-static int normalize(ptycho_plan_s *p, float *obj, float *probe, unsigned upd) {
-    const long no = (long)p->d.obj_ny * p->d.obj_nx, n2 = (long)p->d.n * p->d.n;
+static int normalize_obj(ptycho_plan_s *p, float *obj) {
+    const long no = (long)p->d.obj_ny * p->d.obj_nx;
     Timed tm(p, TC_NORMALIZE);
-    hipLaunchKernelGGL(k_max_partial, dim3(NPART), dim3(256), 0, p->stream, p->denO, (upd & 1u) ? no : 0L,
-                       p->denP, (upd & 2u) ? n2 : 0L, p->part);
-    const long work = std::max((upd & 1u) ? no : 0L, (upd & 2u) ? n2 * p->d.n_modes : 0L);
-    hipLaunchKernelGGL(k_normalize, dim3(grid_for(work)), dim3(256), 0, p->stream,
-                       (float2 *)obj, p->numO, p->denO, no, (float2 *)probe, p->numP, p->denP, (int)n2,
-                       p->d.n_modes, p->part, NPART, p->d.obj_inertia, p->d.probe_inertia, upd);
+    max_object_sums(p);
+    hipLaunchKernelGGL(k_normalize_obj, dim3(grid_for(no)), dim3(256), 0, p->stream, (float2 *)obj, p->numO, p->denO,
+                       no, p->part, p->npartO, p->d.obj_inertia);
     LAUNCHCHK();
     return PTYCHO_OK;
+}
+
+static int normalize_probe(ptycho_plan_s *p, float *probe) {
+    const int n2 = p->d.n * p->d.n;
+    Timed tm(p, TC_NORMALIZE);
+    return with_k(p->d.n_modes, [&](auto kk) {
+        hipLaunchKernelGGL((k_normalize_probe<decltype(kk)::value>), dim3(grid_for(n2)), dim3(256), 0, p->stream,
+                           (float2 *)probe, p->numP, p->denP, n2, p->part + NPART, p->npartP, p->d.probe_inertia,
+                           p->pint);
+        LAUNCHCHK();
+        p->pint_ready = true;
+        return (int)PTYCHO_OK;
+    });
+}
+
+// The state that passes of one call hand on (see ptycho_plan_s) starts afresh.
+static void begin_call(ptycho_plan_s *p) {
+    p->pint_ready = false;
+    p->red_n = 0;
 }
 
 static int check_plan_ptrs(ptycho_plan_t p, const void *a, const void *b) {
@@ -845,9 +908,10 @@ static int run_cycles(ptycho_plan_t p, float *obj, float *probe, float *psi, int
     const NPass *np = passes_for(p->d.n);
     if (!np) return PTYCHO_E_UNSUPPORTED;
     const long n2 = (long)p->d.n * p->d.n;
+    begin_call(p);
     for (int c = 0; c < n_cycles; ++c) {
         int s2 = PTYCHO_OK;
-        if (upd & 1u) s2 = zero_sums(p, ACC_OBJ);
+        if (upd & 1u) s2 = zero_object_sums(p);
         if (!s2) s2 = np->project(p, obj, probe, psi, kind, (upd & 1u) ? ACC_OBJ : 0u, upd_bg, nullptr);
         if (!s2 && upd_bg) {
             // every stack was projected with the old background
@@ -856,9 +920,9 @@ static int run_cycles(ptycho_plan_t p, float *obj, float *probe, float *psi, int
                                (double)p->d.n_frames);
             s2 = hipGetLastError() == hipSuccess ? PTYCHO_OK : fail(PTYCHO_E_HIP, "background update launch");
         }
-        if (!s2 && (upd & 1u)) s2 = normalize(p, obj, probe, 1u);
+        if (!s2 && (upd & 1u)) s2 = normalize_obj(p, obj);
         if (!s2 && (upd & 2u)) s2 = probe_sums(p, obj, (const float2 *)psi, 0, p->d.n_frames, false, false);
-        if (!s2 && (upd & 2u)) s2 = normalize(p, obj, probe, 2u);
+        if (!s2 && (upd & 2u)) s2 = normalize_probe(p, probe);
         // positions: shifts of the projected exit waves against the new
         // object and probe, then the move
         if (!s2 && upd_pos)
@@ -901,20 +965,17 @@ static int forward_pass(ptycho_plan_s *p, int op, const float *obj, const float 
     return np->forward(p, op, obj, probe, dobj, dprobe, icalc, llk_model, keep);
 }
 
-static int zero_red(ptycho_plan_s *p) { return zero_async(p->red, up(sizeof(double) * p->L.nred), p->stream); }
-
-// llk_dev[0] = sum of the reduction partials, llk_dev[1] = number of good pixels
-__global__ void k_copy_scalar(double *dst, const double *src) { dst[0] = src[0]; }
-
-static int llk_into(ptycho_plan_t p, const float *obj, const float *probe, double *llk, int model) {
-    int st = zero_red(p);
-    if (st) return st;
-    st = forward_pass(p, OP_LLK, obj, probe, nullptr, nullptr, nullptr, model);
-    if (st) return st;
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, p->stream, p->red, (long)p->L.nred, 1, llk, 0);
-    hipLaunchKernelGGL(k_copy_scalar, dim3(1), dim3(1), 0, p->stream, llk + 1, p->scal + SC_NOBS);
+// llk[0] = sum of the reduction partials, llk[1] = number of good pixels
+static int write_llk(ptycho_plan_s *p, double *llk, const double *nobs) {
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, p->stream, p->red, p->red_n, 1, llk, nobs);
     LAUNCHCHK();
     return PTYCHO_OK;
+}
+
+static int llk_into(ptycho_plan_t p, const float *obj, const float *probe, double *llk, int model) {
+    begin_call(p);
+    const int st = forward_pass(p, OP_LLK, obj, probe, nullptr, nullptr, nullptr, model);
+    return st ? st : write_llk(p, llk, p->scal + SC_NOBS);
 }
 
 extern "C" int ptycho_llk(ptycho_plan_t p, const float *obj, const float *probe, double *llk) {
@@ -1113,8 +1174,8 @@ extern "C" int ptycho_icalc(ptycho_plan_t p, const float *obj, const float *prob
 // Gradient pass: sums in numO/numP (and denominators), LLK partials in red.
 // keep (nullable) receives the forward row transforms of every frame.
 static int grad_pass(ptycho_plan_s *p, const float *obj, const float *probe, float2 *keep = nullptr) {
-    int st = zero_sums(p, ACC_OBJ | ACC_PROBE);
-    if (!st) st = zero_red(p);
+    p->red_n = 0;
+    const int st = zero_object_sums(p);
     if (st) return st;
     const NPass *np = passes_for(p->d.n);
     if (!np) return PTYCHO_E_UNSUPPORTED;
@@ -1126,31 +1187,25 @@ extern "C" int ptycho_ml_grad(ptycho_plan_t p, const float *obj, const float *pr
     int st = check_prop_ptrs(p, obj, probe);
     if (st) return st;
     if (!g_obj || !g_probe) return fail(PTYCHO_E_INVALID, "null gradient output");
+    begin_call(p);
     st = grad_pass(p, obj, probe);
     if (st) return st;
     const long no = (long)p->d.obj_ny * p->d.obj_nx, np = (long)p->d.n_modes * p->d.n * p->d.n;
-    hipLaunchKernelGGL(k_scale_copy, dim3(grid_for(no)), dim3(256), 0, p->stream, (float2 *)g_obj, p->numO, no, 2.0f);
-    hipLaunchKernelGGL(k_scale_copy, dim3(grid_for(np)), dim3(256), 0, p->stream, (float2 *)g_probe, p->numP, np, 2.0f);
-    if (llk) {
-        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, p->stream, p->red, (long)p->L.nred, 1, llk, 0);
-        hipLaunchKernelGGL(k_copy_scalar, dim3(1), dim3(1), 0, p->stream, llk + 1, p->scal + SC_NOBS);
-    }
+    hipLaunchKernelGGL(k_scale_copy, dim3(grid_for(no + np)), dim3(256), 0, p->stream, (float2 *)g_obj, p->numO, no,
+                       (float2 *)g_probe, p->numP, np, 2.0f);
     LAUNCHCHK();
-    return PTYCHO_OK;
+    return llk ? write_llk(p, llk, p->scal + SC_NOBS) : PTYCHO_OK;
 }
 
 // Line-search coefficients; with keep (the gradient pass's row transforms at
 // the same point) the pass forms and row-transforms only B and C.
 static int ls_pass(ptycho_plan_s *p, const float *obj, const float *probe, const float *dobj, const float *dprobe,
                    double *coef, const float2 *keep = nullptr) {
-    int st = zero_red(p);
-    if (st) return st;
-    st = keep ? forward_pass(p, OP_LS2, obj, probe, dobj, dprobe, nullptr, LLK_POISSON, keep)
+    p->red_n = 0;
+    const int st = keep ? forward_pass(p, OP_LS2, obj, probe, dobj, dprobe, nullptr, LLK_POISSON, keep)
               : forward_pass(p, OP_LS, obj, probe, dobj, dprobe, nullptr);
     if (st) return st;
-    const long n = (long)p->L.nred / 2;
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, p->stream, p->red, n, 2, coef, 0);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, p->stream, p->red + 1, n, 2, coef + 1, 0);
+    hipLaunchKernelGGL(k_sum_partials, dim3(2), dim3(SUM_THREADS), 0, p->stream, p->red, p->red_n, 2, coef, nullptr);
     LAUNCHCHK();
     return PTYCHO_OK;
 }
@@ -1205,15 +1260,15 @@ extern "C" int ptycho_ml_cycle(ptycho_plan_t p, float *obj, float *probe, void *
     b += up(sizeof(float2) * np);
     float2 *g_p = (float2 *)b;
     b += up(sizeof(float2) * np);
-    double *cpart = (double *)b;
-    b += up(sizeof(double) * 4 * CG_NPART);
+    b += up(sizeof(double) * 4 * CG_NPART);       // unused (the partials are in the workspace)
     float2 *keep = (float2 *)b;
     hipStream_t s = p->stream;
     if (reset) {
         hipLaunchKernelGGL(k_cg_reset, dim3(1), dim3(64), 0, s, scal);
         LAUNCHCHK();
     }
-    const long n2 = (long)p->d.n * p->d.n;
+    const int n2 = p->d.n * p->d.n;
+    begin_call(p);
     for (int c = 0; c < n_cycles; ++c) {
         // 1. gradient (sums in numO/numP), LLK, denominators
         p->shifts_in_grad = upd_pos;
@@ -1222,22 +1277,26 @@ extern "C" int ptycho_ml_cycle(ptycho_plan_t p, float *obj, float *probe, void *
         if (st) return st;
         {
         Timed tm(p, TC_OTHER);
-        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, s, p->red, (long)p->L.nred, 1,
-                           scal + CG_LLK, 0);
-        hipLaunchKernelGGL(k_max_partial, dim3(NPART), dim3(256), 0, s, p->denO, (long)no, p->denP, n2, p->part);
+        max_object_sums(p);
         // 2. inner products for beta, then the new direction
-        hipLaunchKernelGGL(k_cg_dots, dim3(CG_NPART), dim3(256), 0, s, p->numO, g_o, (long)no, p->numP, g_p,
-                           (long)np, upd, cpart);
-        hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(256), 0, s, cpart, p->part, NPART, scal, hist ? hist + c : nullptr);
+        const int nd = std::min(grid_for((long)std::max(no, np)), CG_BLOCKS);
+        hipLaunchKernelGGL(k_cg_dots, dim3(nd), dim3(256), 0, s, p->numO, g_o, (long)no, p->numP, g_p, (long)np, upd,
+                           p->cpart);
+        hipLaunchKernelGGL(k_cg_beta, dim3(1), dim3(SUM_THREADS), 0, s, p->red, p->red_n, p->cpart, nd, p->part,
+                           p->npartO, p->part + NPART, p->npartP, scal, hist ? hist + c : nullptr);
         hipLaunchKernelGGL(k_cg_direction, dim3(grid_for((long)std::max(no, np))), dim3(256), 0, s, p->numO, g_o, d_o,
                            (long)no, p->numP, g_p, d_p, (long)np, upd, scal);
         }
         // 3. line search along d, then the step
         st = ls_pass(p, obj, probe, (const float *)d_o, (const float *)d_p, scal + CG_L1, keep);
         if (st) return st;
-        hipLaunchKernelGGL(k_cg_step, dim3(grid_for((long)std::max(no, np))), dim3(256), 0, s, (float2 *)obj, d_o,
-                           (long)no, (float2 *)probe, d_p, (long)np, upd, scal);
-        LAUNCHCHK();
+        st = with_k(p->d.n_modes, [&](auto kk) {
+            hipLaunchKernelGGL((k_cg_step<decltype(kk)::value>), dim3(grid_for((long)std::max(no, np))), dim3(256), 0, s,
+                               (float2 *)obj, d_o, (long)no, (float2 *)probe, d_p, n2, upd, scal, p->pint);
+            LAUNCHCHK();
+            return (int)PTYCHO_OK;
+        });
+        if (st) return st;
         // positions: the shifts the gradient pass took at the cycle's start
         if (upd_pos) {
             st = move_positions(p);
@@ -1344,10 +1403,9 @@ extern "C" int ptycho_llk_noalloc(const ptycho_desc_t *d, const int32_t *offsets
     int *flag = (int *)(base + L.off_flag);
     double *count = (double *)(base + L.off_count);
     const int J = d->n_frames;
-    // every word the call reads is written first: the flag and partials are
-    // cleared by fill kernels, the tables and count are written whole
+    // every word the call reads is written first: the flag is cleared by a
+    // fill kernel, the tables, the count and the partials are written whole
     st = zero_async(flag, ALIGN, s);
-    if (!st) st = zero_async(p.red, up(sizeof(double) * L.nred), s);
     if (st) return st;
     hipLaunchKernelGGL(k_frame_tables, dim3(grid_for(J)), dim3(256), 0, s, (const int *)offsets, J, d->n, d->obj_ny,
                        d->obj_nx, p.offs, p.order, flag);
@@ -1355,8 +1413,8 @@ extern "C" int ptycho_llk_noalloc(const ptycho_desc_t *d, const int32_t *offsets
     LAUNCHCHK();
     st = np->forward(&p, OP_LLK, obj, probe, nullptr, nullptr, nullptr, LLK_POISSON, nullptr);
     if (st) return st;
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(SUM_THREADS), 0, s, p.red, (long)L.nred, 1, llk, 0);
-    hipLaunchKernelGGL(k_copy_scalar, dim3(1), dim3(1), 0, s, llk + 1, count);
+    st = write_llk(&p, llk, count);
+    if (st) return st;
     hipLaunchKernelGGL(k_nan_if_flagged, dim3(1), dim3(1), 0, s, llk, flag);
     LAUNCHCHK();
     return PTYCHO_OK;

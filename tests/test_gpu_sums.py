@@ -1,0 +1,91 @@
+"""The overlap sums and their reductions where their launches branch: tiles
+that no frame covers, split tiles, few and many gather blocks, few and many
+probe chunks, one stack against several, integer and sub-pixel windows; and
+the median of the position update on ties and at odd and even counts."""
+import numpy as np
+import pytest
+
+import oracle
+from cases import make_problem, rel_l2, small
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+UPD = oracle.UPDATE_OBJECT | oracle.UPDATE_PROBE
+TOL = 1e-4          # relative L2 of one cycle, as in the parity tests
+
+
+def device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+@pytest.mark.parametrize("n,k,j,obj,stack", [(16, 1, 2, (150, 61), 0),      # mostly uncovered tiles
+                                             (16, 2, 90, (40, 33), 0),      # every tile split
+                                             (32, 3, 9, (300, 290), 4),     # several stacks
+                                             (64, 1, 700, (1500, 1400), 0), # more than 1024 gather blocks
+                                             (256, 2, 5, (333, 420), 0),    # few probe chunks
+                                             (256, 1, 40, (900, 260), 17)])
+def test_one_cycle_of_each_algorithm(n, k, j, obj, stack):
+    import paper_2008_11511_amd as P
+    dev = device()
+    print(f"[gpu-case] sums n={n} k={k} j={j} obj={obj} stack={stack}", flush=True)
+    step = 0.45 * (min(obj) - n) / np.sqrt(j)
+    pb = make_problem(small("dm256", n=n, k=k, j=j, obj=obj, step=step, mask_frac=0.0), start="ml")
+    to = lambda a, t: torch.from_numpy(np.ascontiguousarray(a)).to(dev, t)  # noqa: E731
+    host = lambda t: t.cpu().numpy()  # noqa: E731
+    plan = P.Plan(pb.offsets, to(pb.iobs, torch.float32), None, k, obj, stack=stack)
+    o, p = to(pb.obj0, torch.complex64), to(pb.probe0, torch.complex64)
+    # fill the workspace's sums with another state's before the checked calls
+    oa, pa = 2 * o, 3 * p
+    plan.ap_cycle(oa, pa, 2, UPD)
+    oa, pa = o.clone(), p.clone()
+    plan.ap_cycle(oa, pa, 2, UPD)
+    ro, rp = pb.obj0, pb.probe0
+    for _ in range(2):
+        ro, rp = oracle.ap_cycle(ro, rp, pb.offsets, pb.iobs, None)
+    assert rel_l2(host(oa), ro) < TOL and rel_l2(host(pa), rp) < TOL
+    go, gp, llk = plan.ml_grad(o, p)
+    ro, rp, rl = oracle.ml_grad(pb.obj0, pb.probe0, pb.offsets, pb.iobs, None)
+    assert rel_l2(host(go), ro) < TOL and rel_l2(host(gp), rp) < TOL
+    assert abs(host(llk)[0] - rl) < TOL * abs(rl) and host(llk)[1] == j * n * n
+    om, pm, st = o.clone(), p.clone(), oracle.CGState()
+    plan.ml_cycle(om, pm, plan.ml_state(), 2, UPD, reset=True)
+    ro, rp = pb.obj0, pb.probe0
+    for _ in range(2):
+        ro, rp = oracle.ml_cycle(ro, rp, st, pb.offsets, pb.iobs, None, UPD)
+    assert rel_l2(host(om), ro) < TOL and rel_l2(host(pm), rp) < TOL
+
+
+@pytest.mark.parametrize("n,j", [(32, 21), (64, 300)])
+def test_sub_pixel_sums_against_the_oracle(n, j):
+    import paper_2008_11511_amd as P
+    dev = device()
+    print(f"[gpu-case] sub-pixel sums n={n} j={j}", flush=True)
+    shape = (6 * n + 5, 9 * n + 2)
+    pos = np.random.default_rng(j).uniform(-2.0 * n, 2.0 * n, (j, 2))
+    offs, frac = oracle.windows_from_positions(pos, n, shape)
+    pb = make_problem(small("dm256", n=n, k=2, j=j, obj=shape, step=1.0, mask_frac=0.0), start="ml")
+    iobs = oracle.simulate_intensity(pb.obj_true, pb.probe_true, offs, frac=frac).astype(np.float32)
+    plan = P.Plan.with_positions(pos, torch.from_numpy(iobs).to(dev), None, 2, shape)
+    o = torch.from_numpy(pb.obj0.astype(np.complex64)).to(dev)
+    p = torch.from_numpy(pb.probe0.astype(np.complex64)).to(dev)
+    plan.ap_cycle(o, p, 1, UPD)
+    ro, rp = oracle.ap_cycle(pb.obj0, pb.probe0, offs, iobs, None, frac=frac)
+    assert rel_l2(o.cpu().numpy(), ro) < TOL and rel_l2(p.cpu().numpy(), rp) < TOL
+
+
+@pytest.mark.parametrize("j", [1, 2, 3, 64, 255, 256, 1024, 2051])
+@pytest.mark.parametrize("ties", [False, True])
+def test_position_update_median(j, ties):
+    from paper_2008_11511_amd.plan import update_positions
+    dev = device()
+    rng = np.random.default_rng(j)
+    sh = rng.standard_normal((j, 3))
+    sh[:, 2] = rng.integers(0, 3, j) * 0.5 if ties else np.abs(sh[:, 2]) * 10.0 ** rng.integers(-9, 9, j)
+    pos0 = rng.uniform(-50, 50, (j, 2))
+    pos = pos0 + rng.uniform(-1, 1, (j, 2))
+    for min_grad in (0.1, 1.0):
+        got = update_positions(*(torch.from_numpy(a).to(dev) for a in (pos, pos0, sh)), 1.0, 2.0, min_grad)
+        ref = oracle.update_positions(pos, pos0, sh[:, :2], sh[:, 2], 1.0, 2.0, min_grad)
+        assert np.array_equal(got.cpu().numpy(), ref)
