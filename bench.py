@@ -230,7 +230,7 @@ PROFILE_SPECS = {
         "classes": {"rows_fwd": "void ptycho::k_rows_fwd<256, 1, false, false>",
                     "cols": "void ptycho::k_cols_joint<256, 3, 5, false>",
                     "rows_inv": "void ptycho::k_rows_inv<256, 3, 1, true, false, false>",
-                    "gather_obj": "void ptycho::k_gather_obj<false, 4>",
+                    "gather_obj": "ptycho::k_gather_obj",
                     "probe_all": "void ptycho::k_gather_probe<3, false>"}},
     "ml256_ml_cycle": {
         "title": "conjugate-gradient ML cycle, 500 frames 256x256, 3 modes (ml256)",
@@ -238,7 +238,7 @@ PROFILE_SPECS = {
         "classes": {"rows_fwd": "void ptycho::k_rows_fwd<256, 0, false, false>",
                     "cols": "void ptycho::k_cols_joint<256, 3, 1, false>",
                     "rows_inv": "void ptycho::k_rows_inv<256, 3, 0, true, false, false>",
-                    "gather_obj": "void ptycho::k_gather_obj<false, 4>",
+                    "gather_obj": "ptycho::k_gather_obj",
                     "gather_probe": "void ptycho::k_gather_probe<3, true>",
                     "ls_rows": "void ptycho::k_rows_fwd<256, 4, false, false>",
                     "ls_cols": "void ptycho::k_cols_seq<256, 6, false>"}},
@@ -250,7 +250,7 @@ PROFILE_SPECS = {
                     "rows_inv": "void ptycho::k_rows_inv<512, 4, 1, true, false, false>",
                     "ap_cols": "void ptycho::k_cols_joint<512, 4, 0, false>",
                     "ap_rows_inv": "void ptycho::k_rows_inv<512, 4, 2, true, false, false>",
-                    "gather_obj": "void ptycho::k_gather_obj<false, 4>",
+                    "gather_obj": "ptycho::k_gather_obj",
                     "probe_all": "void ptycho::k_gather_probe<4, false>"}},
     "nf2048_dm_cycle": {
         "title": "near-field DM cycle, 17 frames 2048x2048, 1 mode (nf2048)",
@@ -258,7 +258,7 @@ PROFILE_SPECS = {
         "classes": {"rows_fwd": "void ptycho::k_rows_fwd<2048, 1, true, false>",
                     "cols": "void ptycho::k_cols_joint<2048, 1, 5, true>",
                     "rows_inv": "void ptycho::k_rows_inv<2048, 1, 1, true, true, false>",
-                    "gather_obj": "void ptycho::k_gather_obj<false, 4>",
+                    "gather_obj": "ptycho::k_gather_obj",
                     "probe_all": "void ptycho::k_gather_probe<1, false>"}},
 }
 
@@ -304,7 +304,9 @@ def _dispatches(rows, counter=None):
 def _select(disp, spec):
     """Values of each class's full-size launches inside the cycle's window."""
     def named(d, k):
-        return d[1].startswith(k + "(") if k.startswith("void ") else d[1].startswith(k)
+        if k.startswith("void "):
+            return d[1].startswith(k + "(")
+        return (d[1][5:] if d[1].startswith("void ") else d[1]).startswith(k)     # any template instance
     ids = [d[0] for d in disp if any(named(d, k) for k in spec["anchors"])]
     if not ids:
         return {}
