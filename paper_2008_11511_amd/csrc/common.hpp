@@ -206,6 +206,23 @@ struct StackArgs {
 };
 
 
+// Bit e: whether pixel at(e) is masked.  All bytes are loaded under one branch
+// before the first is looked at; a branch around each load makes the thread
+// wait for one byte after the other, a memory latency each (500 x 256^2 x
+// 3-mode ML cycle 2.15 -> 2.00 ms, 800 x 512^2 x 4-mode AP cycle 11.3 -> 10.6).
+template <int E, class At>
+__device__ __forceinline__ unsigned mask_bits(const unsigned char *mask, At at) {
+    unsigned bits = 0;
+    if (mask != nullptr) {
+        unsigned char v[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = mask[at(e)];
+#pragma unroll
+        for (int e = 0; e < E; ++e) bits |= v[e] != 0 ? 1u << e : 0u;
+    }
+    return bits;
+}
+
 // --------------------------------------------------------- reductions -----
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll

@@ -245,8 +245,15 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs 
         frame_forward<N>(u[m], C, th.t, R, th.tr);
     }
 
-    // intensity -> scale of the pixels (r, x) this thread owns
-    float sc[E];
+    // the data of the pixels (r, x) this thread owns, then intensity -> scale
+    float iobv[E], sc[E];
+    auto pixel = [&](int e) { return (unsigned)(th.r * N + th.tr) + elem_const<N, E, LastRadix<N, E, -1>::value>(e); };
+    {
+        const float *io = a.iobs + (size_t)th.j * n2;
+#pragma unroll
+        for (int e = 0; e < E; ++e) iobv[e] = io[pixel(e)];
+    }
+    const unsigned bad_bits = mask_bits<E>(a.mask, pixel);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         sc[e] = 0.0f;
@@ -270,14 +277,18 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs 
     }
     double acc = 0.0;
     {
-        const float *io = a.iobs + (size_t)th.j * n2;
-        const unsigned at = th.r * N + th.tr;
+#pragma unroll
+        for (int e = 0; e < E; ++e) sc[e] *= nrm;
+        if (a.bg != nullptr) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) sc[e] += a.bg[pixel(e)];
+        }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const unsigned x = at + elem_const<N, E, LastRadix<N, E, -1>::value>(e);
-            const float inten = sc[e] * nrm + (a.bg != nullptr ? a.bg[x] : 0.0f);
-            const bool bad = a.mask != nullptr && a.mask[x] != 0;
-            const float iob = io[x];
+            const unsigned x = pixel(e);
+            const float inten = sc[e];
+            const bool bad = (bad_bits >> e) & 1u;
+            const float iob = iobv[e];
             if constexpr (OP == OP_PROJECT) {
                 const float q = iob / fmaxf(inten, a.eps);
                 sc[e] = bad ? nrm : sqrtf(q) * nrm;
@@ -444,20 +455,31 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame_read(Stack
     }
 
     const float *io = a.iobs + (size_t)th.j * n2;
-    const unsigned at = th.r * N + th.tr;
+    auto pixel = [&](int e) { return (unsigned)(th.r * N + th.tr) + elem_const<N, E, LastRadix<N, E, -1>::value>(e); };
+    float iobv[E];
+    unsigned bad_bits = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        i0[e] *= nrm;
+        if constexpr (OP != OP_ICALC) iobv[e] = io[pixel(e)];
+    }
+    if constexpr (OP != OP_ICALC) bad_bits = mask_bits<E>(a.mask, pixel);
+    if (a.bg != nullptr) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) i0[e] += a.bg[pixel(e)];
+    }
     double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         // each mode's threads take the pixels of their elements e = k, k + K, ...
         if (KG > 1 && e % KG != th.k) continue;
-        const unsigned x = at + elem_const<N, E, LastRadix<N, E, -1>::value>(e);
-        const float inten = i0[e] * nrm + (a.bg != nullptr ? a.bg[x] : 0.0f);
+        const unsigned x = pixel(e);
+        const float inten = i0[e];
         if constexpr (OP == OP_ICALC) {
             if (th.active) (a.icalc + (size_t)th.j * n2)[x] = inten;
         } else {
-            const bool bad = a.mask != nullptr && a.mask[x] != 0;
-            if (bad || !th.active) continue;
-            const float iob = io[x];
+            if (((bad_bits >> e) & 1u) || !th.active) continue;
+            const float iob = iobv[e];
             const float ifl = fmaxf(inten, a.eps);
             if constexpr (OP == OP_LLK) {
                 acc0 += (double)llk_model_term(a.llk_model, ifl, iob);

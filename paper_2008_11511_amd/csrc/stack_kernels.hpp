@@ -298,14 +298,10 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS, (ColMinWaves<N, K, OP, NF>::va
     // the data of the pixels this thread will own after the transform are
     // loaded now: loads cannot move across the transform's barriers
     const float *io = a.iobs + (size_t)j * N * N + c;
+    const unsigned bad_bits = mask_bits<E>(a.mask, [&](int e) { return det_row<N, E, NF>(t, e) * N + c; });
     float iobv[E];
-    bool badv[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int q = det_row<N, E, NF>(t, e);
-        iobv[e] = io[(size_t)q * N];
-        badv[e] = a.mask != nullptr && a.mask[q * N + c] != 0;
-    }
+    for (int e = 0; e < E; ++e) iobv[e] = io[(size_t)det_row<N, E, NF>(t, e) * N];
     col_transforms<N, E, -1, K, SEQ>(u, t, L);
     if constexpr (NF) {
         // Dy: to the detector plane
@@ -314,16 +310,25 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS, (ColMinWaves<N, K, OP, NF>::va
         col_transforms<N, E, +1, K, SEQ>(u, t1, L);
     }
 
+    float in[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        in[e] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) in[e] += cnorm(u[k][e]);
+        in[e] *= nrm;
+    }
+    // the background (L2-resident, usually absent) is read here rather than
+    // with Iobs, so that it holds no registers across the transform
+    if (a.bg != nullptr) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) in[e] += a.bg[det_row<N, E, NF>(t, e) * N + c];
+    }
     double acc = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        float inten = 0.0f;
-#pragma unroll
-        for (int k = 0; k < K; ++k) inten += cnorm(u[k][e]);
-        // the background (L2-resident, usually absent) is read here rather
-        // than with Iobs, so that it holds no registers across the transform
-        inten = inten * nrm + (a.bg != nullptr ? a.bg[det_row<N, E, NF>(t, e) * N + c] : 0.0f);
-        const bool bad = badv[e];
+        const float inten = in[e];
+        const bool bad = (bad_bits >> e) & 1u;
         const float iob = iobv[e];
         float sc;
         if constexpr (OP == OP_PROJECT) {
@@ -453,17 +458,30 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS) void k_cols_seq(StackArgs a) {
         }
     }
     const float *io = a.iobs + (size_t)j * N * N + c;
+    // all data are loaded before the first are used
+    float iobv[E];
+    unsigned bad_bits = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        i0[e] *= nrm;
+        if constexpr (OP != OP_ICALC) iobv[e] = io[(size_t)det_row<N, E, NF>(t, e) * N];
+    }
+    if constexpr (OP != OP_ICALC)
+        bad_bits = mask_bits<E>(a.mask, [&](int e) { return det_row<N, E, NF>(t, e) * N + c; });
+    if (a.bg != nullptr) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) i0[e] += a.bg[det_row<N, E, NF>(t, e) * N + c];
+    }
     double acc0 = 0.0, acc1 = 0.0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int q = det_row<N, E, NF>(t, e);
-        const float inten = i0[e] * nrm + (a.bg != nullptr ? a.bg[q * N + c] : 0.0f);
+        const float inten = i0[e];
         if constexpr (OP == OP_ICALC) {
             if (active) a.icalc[((size_t)j * N + q) * N + c] = inten;
         } else {
-            const bool bad = a.mask != nullptr && a.mask[q * N + c] != 0;
-            if (bad || !active) continue;
-            const float iob = io[(size_t)q * N];
+            if (((bad_bits >> e) & 1u) || !active) continue;
+            const float iob = iobv[e];
             const float ifl = fmaxf(inten, a.eps);
             if constexpr (OP == OP_LLK) {
                 acc0 += (double)llk_model_term(a.llk_model, ifl, iob);
