@@ -38,6 +38,18 @@ constexpr int col_e(int n) { return (n == 16 || n >= 2048) ? 16 : 8; }
 constexpr int col_cb(int n) {
     return (n >= 1024) ? 4 : (n >= 256) ? 8 : ((256 / (n / col_e(n))) > 16 ? 256 / (n / col_e(n)) : 16);
 }
+// Columns per block of the joint pass (all modes in registers) and of the
+// read-only pass's line search.  Where a 512-thread block of whole tiles leaves
+// no room for a second block on the CU, half a tile per 256-thread block does:
+// the blocks' barriers and memory phases then overlap.  512 points, 4 modes
+// (156 registers): columns of 800 frames 4.08 -> 2.87 ms; line search at 512
+// points (173 registers): 400 frames of 4 modes 2.49 -> 2.05 ms; 2048 points: 20
+// far-field frames 564 -> 449 us, 17 near-field ones 605 -> 568 us.  With up to 3 modes at 512 points, in the other read-only
+// passes and at 1024 points two whole-tile blocks fit, and reading full 64-byte
+// rows is faster (512, 2 modes: 348 against 381 us; intensities 149 / 227).
+constexpr int joint_cb(int n, int k) { return (n == 512 && k >= 4) ? 4 : n >= 2048 ? 2 : col_cb(n); }
+constexpr int seq_cb(int n, bool ls) { return (n == 512 && ls) ? 4 : col_cb(n); }
+constexpr int min_cb(int n) { return joint_cb(n, 4) < seq_cb(n, true) ? joint_cb(n, 4) : seq_cb(n, true); }
 constexpr int scr_tile_w(int n) { return col_cb(n) < n ? col_cb(n) : n; }
 
 // Row transforms: 16 elements per thread from N = 128 up (fewer LDS passes),
@@ -60,11 +72,12 @@ struct InvRowGeom {
 // Column transforms keep all K modes in registers at once, so they use 8
 // elements per thread (16 at N = 16 and N = 2048), CB adjacent columns per
 // block (a 128-byte row segment at CB = 16; 4 columns from N = 1024 keep the
-// block at 512 threads, so that a thread may hold 256 registers).
-template <int N>
+// block at 512 threads, so that a thread may hold 256 registers).  Some passes
+// take half a column tile per block (see joint_cb and seq_cb).
+template <int N, int CB_ = col_cb(N)>
 struct ColGeom {
     static constexpr int E = col_e(N), T = N / E;
-    static constexpr int CB = col_cb(N);
+    static constexpr int CB = CB_;
     static constexpr int THREADS = CB * T;
     static constexpr int LDS_F2 = (FftCfg<N, E>::P > 1) ? N * CB : 1;   // one transform buffer
 };
@@ -76,7 +89,8 @@ struct ColGeom {
 // (measured faster at 256 points with 3 modes and at 512 points).
 template <int N, int K>
 struct ColJoint {
-    static constexpr bool SEQ = (size_t)K * ColGeom<N>::LDS_F2 * 8 > 32 * 1024;
+    using G = ColGeom<N, joint_cb(N, K)>;
+    static constexpr bool SEQ = (size_t)K * G::LDS_F2 * 8 > 32 * 1024;
     static constexpr int BUFS = SEQ ? 1 : K;
 };
 

@@ -21,25 +21,28 @@ template <int N>
 static int rows_blocks(int sn) {
     return (int)(((long)sn * N + RowGeom<N>::RB - 1) / RowGeom<N>::RB);
 }
-template <int N>
+template <int N, class G>
 static int cols_blocks(int sn) {
-    return (int)(((long)sn * N + ColGeom<N>::CB - 1) / ColGeom<N>::CB);
+    return (int)(((long)sn * N + G::CB - 1) / G::CB);
 }
 
 template <int N, int K, int OP, bool NF>
 static void launch_cols_joint(const StackArgs &a, hipStream_t s) {
-    const size_t lds = sizeof(float2) * ColGeom<N>::LDS_F2 * ColJoint<N, K>::BUFS;
+    using G = typename ColJoint<N, K>::G;
+    const size_t lds = sizeof(float2) * G::LDS_F2 * ColJoint<N, K>::BUFS;
     static const hipError_t attr = set_dyn_lds(k_cols_joint<N, K, OP, NF>, lds);
     (void)attr;
-    hipLaunchKernelGGL((k_cols_joint<N, K, OP, NF>), dim3(cols_blocks<N>(a.S)), dim3(ColGeom<N>::THREADS), lds, s,
-                       a);
+    const dim3 grid(cols_blocks<N, G>(a.S)), block(G::THREADS);
+    hipLaunchKernelGGL((k_cols_joint<N, K, OP, NF>), grid, block, lds, s, a);
 }
 template <int N, int OP, bool NF>
 static void launch_cols_seq(const StackArgs &a, hipStream_t s) {
-    const size_t lds = sizeof(float2) * ColGeom<N>::LDS_F2 * ColSeqBufs<N, OP>::value;
+    using G = typename ColSeqBufs<N, OP>::G;
+    const size_t lds = sizeof(float2) * G::LDS_F2 * ColSeqBufs<N, OP>::value;
     static const hipError_t attr = set_dyn_lds(k_cols_seq<N, OP, NF>, lds);
     (void)attr;
-    hipLaunchKernelGGL((k_cols_seq<N, OP, NF>), dim3(cols_blocks<N>(a.S)), dim3(ColGeom<N>::THREADS), lds, s, a);
+    const dim3 grid(cols_blocks<N, G>(a.S)), block(G::THREADS);
+    hipLaunchKernelGGL((k_cols_seq<N, OP, NF>), grid, block, lds, s, a);
 }
 
 // Forward row pass of input form MODE: the sub-pixel-window instance when the
@@ -156,7 +159,7 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
                 else launch_frame<N, K, OP_PROJECT>(a, s);
             }
         } else {
-            if (kind == 2) p->red_n += cols_blocks<N>(sn);
+            if (kind == 2) p->red_n += cols_blocks<N, typename ColJoint<N, K>::G>(sn);
             const dim3 rg(rows_blocks<N>(sn), p->d.n_modes);
             {
                 Timed tm(p, TC_ROWS_FWD);
@@ -222,7 +225,7 @@ static int forward_pass_op(ptycho_plan_s *p, const float *obj, const float *prob
         a.icalc = icalc;
         a.llk_model = llk_model;
         a.red = p->red + p->red_n * (ls ? 2 : 1);
-        p->red_n += cols_blocks<N>(sn);
+        p->red_n += cols_blocks<N, typename ColSeqBufs<N, OP>::G>(sn);
         if (OP == OP_LS2) a.colin = keep + (size_t)s0 * p->d.n_modes * N * N;
         const dim3 rg(rows_blocks<N>(sn), p->d.n_modes);
         {

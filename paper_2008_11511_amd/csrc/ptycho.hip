@@ -146,7 +146,7 @@ static Layout layout_for(const ptycho_desc_t &d) {
     // the scratch holds max(S, 3 S_ls) frame-modes per mode; two sets per slot
     L.S_ls2 = std::max(1, std::min(J, std::max(L.S, 3 * L.S_ls) / 2));
     L.nstacks_ls2 = (J + L.S_ls2 - 1) / L.S_ls2;
-    const int cb = col_cb(N);
+    const int cb = min_cb(N);
     L.maxb = (int)(((long)L.S * N + cb - 1) / cb);
     L.maxb_ls = (int)(((long)L.S_ls * N + cb - 1) / cb);
     L.maxb_ls2 = (int)(((long)L.S_ls2 * N + cb - 1) / cb);

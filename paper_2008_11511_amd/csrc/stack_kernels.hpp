@@ -213,17 +213,21 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
 template <int N, int OP>
 struct ColSeqBufs {
     static constexpr int SETS = (OP == OP_LS || OP == OP_LS2) ? 3 : 1;
+    using G = ColGeom<N, seq_cb(N, SETS == 3)>;
     static constexpr int value = ((size_t)SETS * ColGeom<N>::LDS_F2 * 8 <= 96 * 1024) ? SETS : 1;
 };
 
-// Waves per SIMD a column kernel is compiled for: the DM form with up to 3
-// modes fits 128 registers without spilling, which gives 4 waves instead of
-// 3 (measured faster); the near-field pass at 2048 points with one mode gets
-// 4 waves too, so that two of its 512-thread blocks share a CU (a 32-byte
-// spill; measured faster); the others keep the compiler's choice.
+// Waves per SIMD a column kernel is compiled for: up to 3 modes the DM and
+// gradient forms fit 128 registers without spilling and the 512-point
+// projection with 12 bytes of spill, which gives 4 waves instead of 3 (two
+// 512-thread blocks instead of one at 512 points, 3 modes: AP columns of 150
+// frames 533 -> 362 us); the 256-point, 3-mode projection would spill 56 bytes
+// and is faster at 3 waves (299 against 364 us, 500 frames).  The near-field
+// pass at 2048 points with one mode gets 4 waves too.  The others keep the
+// compiler's choice.
 template <int N, int K, int OP, bool NF>
 struct ColMinWaves {
-    static constexpr int value = ((!NF && ColJoint<N, K>::SEQ && N <= 256 && K <= 3 && OP == OP_CORR) ||
+    static constexpr int value = ((!NF && ColJoint<N, K>::SEQ && N <= 512 && K <= 3 && (N == 512 || OP != OP_PROJECT)) ||
                                   (NF && N >= 2048 && K == 1)) ? 4 : 1;
 };
 
@@ -262,8 +266,8 @@ __device__ __forceinline__ void apply_qy(float2 (&u)[K][E], const float2 *qy, in
 // Column FFTs of all K modes held together in registers, the Fourier-space
 // step and (project / grad) the inverse column FFTs, written back in place.
 template <int N, int K, int OP, bool NF>
-__global__ __launch_bounds__(ColGeom<N>::THREADS, (ColMinWaves<N, K, OP, NF>::value)) void k_cols_joint(StackArgs a) {
-    using G = ColGeom<N>;
+__global__ __launch_bounds__((ColJoint<N, K>::G::THREADS), (ColMinWaves<N, K, OP, NF>::value)) void k_cols_joint(StackArgs a) {
+    using G = typename ColJoint<N, K>::G;
     constexpr int E = G::E, CB = G::CB;
     extern __shared__ float2 lds_dyn[];
     const int tid = threadIdx.x, cl = tid % CB, t = tid / CB;
@@ -284,7 +288,8 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS, (ColMinWaves<N, K, OP, NF>::va
     // far field from 512 points (two waves per SIMD, latency-bound) the stack
     // is read non-temporally: 4000 x 512^2 x 4 modes, columns 25.2 -> 23.8 ms
     // per DM cycle; at 256 points it made the pass 5% slower
-    constexpr bool NT = !NF && N >= 512;
+    // (not for half tiles: the other half of a line goes to another block)
+    constexpr bool NT = !NF && N >= 512 && CB == ScrTile<N>::W;
     float2 u[K][E];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -372,8 +377,8 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS, (ColMinWaves<N, K, OP, NF>::va
 // transforms' inputs are read once, non-temporally (line search at 500 x
 // 256^2 x 3 modes: ML cycle 2.34 -> 2.31 ms).
 template <int N, int OP, bool NF>
-__global__ __launch_bounds__(ColGeom<N>::THREADS) void k_cols_seq(StackArgs a) {
-    using G = ColGeom<N>;
+__global__ __launch_bounds__((ColSeqBufs<N, OP>::G::THREADS)) void k_cols_seq(StackArgs a) {
+    using G = typename ColSeqBufs<N, OP>::G;
     constexpr int E = G::E, CB = G::CB;
     extern __shared__ float2 lds_dyn[];
     const int tid = threadIdx.x, cl = tid % CB, t = tid / CB;
@@ -387,6 +392,9 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS) void k_cols_seq(StackArgs a) {
     constexpr int SETS = ColSeqBufs<N, OP>::SETS;
     constexpr bool ONE_BUF = ColSeqBufs<N, OP>::value == 1 && SETS > 1;
 
+    // whole tiles are read once; the other half of a half tile's lines goes to
+    // another block
+    auto ld_col = [](const float2 *p) { return CB == ScrTile<N>::W ? ld_stream(p) : *p; };
     float i0[E], i1[E], i2[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) i0[e] = i1[e] = i2[e] = 0.0f;
@@ -411,7 +419,7 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS) void k_cols_seq(StackArgs a) {
             auto load_transform = [&](float2 (&v)[1][E], int set) {
                 const float2 *src = src_of(set, k);
 #pragma unroll
-                for (int e = 0; e < E; ++e) v[0][e] = ld_stream(src + in_index<N, E, -1>(t, e) * ScrTile<N>::W);
+                for (int e = 0; e < E; ++e) v[0][e] = ld_col(src + in_index<N, E, -1>(t, e) * ScrTile<N>::W);
                 const int t0 = opaque(t);
                 col_transforms<N, E, -1, 1, false>(v, t0, Ls);
                 if constexpr (NF) {
@@ -438,7 +446,7 @@ __global__ __launch_bounds__(ColGeom<N>::THREADS) void k_cols_seq(StackArgs a) {
         for (int set = 0; set < SETS; ++set) {
             const float2 *src = src_of(set, k);
 #pragma unroll
-            for (int e = 0; e < E; ++e) u[set][e] = ld_stream(src + in_index<N, E, -1>(t, e) * ScrTile<N>::W);
+            for (int e = 0; e < E; ++e) u[set][e] = ld_col(src + in_index<N, E, -1>(t, e) * ScrTile<N>::W);
         }
         col_transforms<N, E, -1, SETS, ONE_BUF>(u, t, Ls);
         if constexpr (NF) {
