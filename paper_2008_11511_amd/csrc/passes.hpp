@@ -117,13 +117,26 @@ static void launch_frame_read(const StackArgs &a, hipStream_t s) {
     hipLaunchKernelGGL((k_frame_read<N, K, OP, SUB>), grid, block, lds, s, a);
 }
 
+// Whether the gradient's inverse rows take the probe sums (k_rows_inv_grad),
+// from 128 points on, where a block's rows belong to one frame: integer
+// windows only, whose view the kernel reads, and not where position shifts
+// need the gradient waves in the scratch.
+static bool grad_rows(const ptycho_plan_s *p, const StackArgs &a) {
+    return a.frac == nullptr && !p->shifts_in_grad;
+}
+template <int N, int K, bool NF>
+static void launch_rows_inv_grad(ptycho_plan_s *p, const StackArgs &a, int chunks, hipStream_t s) {
+    const dim3 grid((unsigned)(N / InvRowGeom<N>::RQ * chunks)), block(InvRowGeom<N>::TPM * K);
+    hipLaunchKernelGGL((k_rows_inv_grad<N, K, NF>), grid, block, 0, s, a, chunks, p->pnum, p->pden);
+}
+
 // One pass over all stacks: forward rows, column op, inverse rows and the
 // per-stack gathers.  kind: 0 = AP projection, 1 = DM, 2 = ML gradient.
 // Exit waves go to `psi` (all frames) when it is given, else stay in the
 // stack scratch.  acc selects the sums taken per stack: the object sums
 // (from the inverse row pass's per-frame terms), the probe sums (only for
-// the gradient, whose two sums are taken at the same point; they read the
-// exit waves from the scratch).
+// the gradient, whose two sums are taken at the same point; by the inverse
+// row pass itself or from the exit waves in the scratch).
 template <int N, int K, bool NF>
 static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *probe, float *psi, int kind,
                            unsigned acc, bool upd_bg, float2 *keep) {
@@ -146,6 +159,8 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         if (keep) a.fwd = keep + (size_t)s0 * K * N * N;
         a.colin = a.fwd;
         const bool whole = !NF && by_frame<N, K>(p, keep);
+        bool probe_done = false;
+        const int chunks = std::max(1, std::min(p->L.gchunks, sn));
         if (whole) {
             if constexpr (has_frame<N, K>() && !NF) {
                 if (!wq) a.qbuf = nullptr;
@@ -174,7 +189,10 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
             }
             {
                 Timed tm(p, TC_ROWS_INV);
-                if (kind == 1) launch_rows_inv<N, K, OUT_DM, NF>(a, wq, s);
+                if constexpr (N >= 128) probe_done = kind == 2 && grad_rows(p, a);
+                if (probe_done) {
+                    if constexpr (N >= 128) launch_rows_inv_grad<N, K, NF>(p, a, chunks, s);
+                } else if (kind == 1) launch_rows_inv<N, K, OUT_DM, NF>(a, wq, s);
                 else if (store) launch_rows_inv<N, K, OUT_STORE, NF>(a, wq, s);
                 else if (acc & ACC_PROBE) launch_rows_inv<N, K, OUT_SCR, NF>(a, wq, s);
                 else launch_rows_inv<N, K, OUT_NONE, NF>(a, wq, s);
@@ -190,7 +208,8 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         // ML position shifts from the gradient wave left in the scratch
         if (kind == 2 && p->shifts_in_grad) st = launch_ml_shifts(p, obj, probe, s0, sn);
         if (!st && (acc & ACC_OBJ)) st = object_sums(p, sidx);
-        if (!st && (acc & ACC_PROBE)) st = probe_sums(p, obj, p->scr, s0, sn, true, sidx > 0);
+        if (!st && probe_done) st = reduce_probe(p, chunks, sidx > 0);
+        else if (!st && (acc & ACC_PROBE)) st = probe_sums(p, obj, p->scr, s0, sn, true, sidx > 0);
         if (st) return st;
     }
     return PTYCHO_OK;

@@ -56,6 +56,7 @@ struct Layout {
         off_numP, off_denP, off_pnum, off_pden, off_part, off_red, off_scal, off_s2, off_bsum, off_prop,
         off_pspart, off_shift, off_pos, off_pos0, off_frac, off_bmax, off_cpart, total;
     int pos_chunks;               // row chunks per frame of the position-shift sums
+    int gchunks;                  // frame chunks of the gradient's inverse row pass
 };
 
 // Per-kernel-class timing with HIP events on the plan's stream.
@@ -173,6 +174,7 @@ StackArgs stack_args(ptycho_plan_s *p, int s0, int sn, const float *obj, const f
 int object_sums(ptycho_plan_s *p, int sidx);
 int probe_sums(ptycho_plan_s *p, const float *obj, const float2 *psi, int q0, int nq, bool from_scr,
                bool accumulate);
+int reduce_probe(ptycho_plan_s *p, int chunks, bool accumulate);
 int need_probe_intensity(ptycho_plan_s *p, const float *probe);
 int launch_bg_accum(ptycho_plan_s *p, int sn, int first);
 // ML position shifts of the stack's slots s0 .. s0+sn from the gradient wave

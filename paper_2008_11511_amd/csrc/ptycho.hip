@@ -109,6 +109,20 @@ static int probe_chunks(const ptycho_desc_t &d) {
     return (int)std::min<long>(c, d.n_frames);
 }
 
+// Frame chunks of the gradient's inverse row pass (k_rows_inv_grad), of at
+// least two frames each.  Its registers allow 8 wavefronts per CU: up to 512
+// points the blocks are one round of that (256 x 3 modes, 500 frames: 326 us
+// in one round, 443 in one and a third, 336 in two, 352 in six).  Larger
+// frames leave a block so many rows and so few frames that unequal blocks
+// count: six rounds (1024 x 1, 100 frames: 838 us in one round, 684 in six).
+static int grad_chunks(const ptycho_desc_t &d) {
+    if (d.n < 128) return 0;
+    const int T = d.n / row_e(d.n), tpm = std::max(64, T);
+    const long resident = 256L * (8 / (tpm / 64 * d.n_modes)), rows = (long)d.n / (tpm / T);
+    const long c = std::max(1L, std::min((d.n <= 512 ? 1 : 6) * resident / rows, 64L));
+    return (int)std::max(1L, std::min(c, (long)d.n_frames / 2));
+}
+
 // Object margin of a frame's tile coverage: windows of a positions plan move
 // up to max_shift pixels and view one more row and column.
 static int window_margin(const ptycho_desc_t &d) {
@@ -166,6 +180,8 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.nred = std::max({(size_t)L.nstacks * L.maxb, (size_t)L.nstacks_ls * L.maxb_ls * 2,
                        (size_t)L.nstacks_ls2 * L.maxb_ls2 * 2});
     L.pchunks = probe_chunks(d);
+    L.gchunks = grad_chunks(d);
+    const size_t nchunks = std::max(L.pchunks, L.gchunks);
     L.pos_chunks = N / pos_rows(N);
     const size_t n2 = (size_t)N * N, no = (size_t)d.obj_ny * d.obj_nx;
     size_t o = 0;
@@ -181,8 +197,8 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.off_denO = o; o = up(o + sizeof(float) * no);
     L.off_numP = o; o = up(o + sizeof(float2) * K * n2);
     L.off_denP = o; o = up(o + sizeof(float) * n2);
-    L.off_pnum = o; o = up(o + sizeof(float2) * (size_t)L.pchunks * K * n2);
-    L.off_pden = o; o = up(o + sizeof(float) * (size_t)L.pchunks * n2);
+    L.off_pnum = o; o = up(o + sizeof(float2) * nchunks * K * n2);
+    L.off_pden = o; o = up(o + sizeof(float) * nchunks * n2);
     L.off_part = o; o = up(o + sizeof(float) * 2 * NPART);
     L.off_red = o; o = up(o + sizeof(double) * L.nred);
     L.off_scal = o; o = up(o + sizeof(double) * NSCAL);
@@ -786,15 +802,23 @@ int ptycho::probe_sums(ptycho_plan_s *p, const float *obj, const float2 *psi, in
         else hipLaunchKernelGGL((k_gather_probe<K, false>), grid, dim3(256), 0, p->stream, a);
         return (int)PTYCHO_OK;
     });
+    return reduce_probe(p, chunks, accumulate);
+}
+
+// The probe sums from the partials of `chunks` frame chunks, and their
+// denominators' maxima.
+int ptycho::reduce_probe(ptycho_plan_s *p, int chunks, bool accumulate) {
+    const int K = p->d.n_modes;
+    const long n2 = (long)p->d.n * p->d.n;
     // chunk groups side by side where there are many chunks of few values
     const int G = chunks >= 8 ? 4 : 1;
-    p->npartP = (int)std::max(1L, std::min((n2 * a.K * G + 255) / 256, (long)NPART));
+    p->npartP = (int)std::max(1L, std::min((n2 * K * G + 255) / 256, (long)NPART));
     if (G == 4)
         hipLaunchKernelGGL((k_probe_reduce<4>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
-                           a.K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
+                           K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
     else
         hipLaunchKernelGGL((k_probe_reduce<1>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
-                           a.K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
+                           K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
     LAUNCHCHK();
     return PTYCHO_OK;
 }

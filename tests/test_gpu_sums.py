@@ -57,6 +57,31 @@ def test_one_cycle_of_each_algorithm(n, k, j, obj, stack):
     assert rel_l2(host(om), ro) < TOL and rel_l2(host(pm), rp) < TOL
 
 
+@pytest.mark.parametrize("n,k,j,stack", [(128, 3, 1, 0),       # one frame, one chunk
+                                         (128, 4, 67, 0),      # more chunks than pairs of frames
+                                         (128, 3, 41, 3),      # a last stack shorter than the chunks
+                                         (256, 3, 37, 0),      # chunks of unequal length
+                                         (256, 1, 3, 2),
+                                         (512, 4, 5, 0),
+                                         (512, 3, 7, 4),
+                                         (1024, 1, 5, 0),
+                                         (2048, 1, 2, 0)])
+def test_gradient_with_the_sums_in_its_row_pass(n, k, j, stack):
+    import paper_2008_11511_amd as P
+    dev = device()
+    print(f"[gpu-case] gradient rows n={n} k={k} j={j} stack={stack}", flush=True)
+    shape = (n + 45, n + 61)
+    pb = make_problem(small("ml256", n=n, k=k, j=j, obj=shape, step=20.0 / np.sqrt(j), mask_frac=0.03), start="ml")
+    to = lambda a, t: torch.from_numpy(np.ascontiguousarray(a)).to(dev, t)  # noqa: E731
+    plan = P.Plan(pb.offsets, to(pb.iobs, torch.float32), to(pb.mask, torch.uint8), k, shape, stack=stack)
+    o, p = to(pb.obj0, torch.complex64), to(pb.probe0, torch.complex64)
+    plan.ml_grad(2 * o, 3 * p)            # fill the partial sums with another state's
+    go, gp, llk = plan.ml_grad(o, p)
+    ro, rp, rl = oracle.ml_grad(pb.obj0, pb.probe0, pb.offsets, pb.iobs, pb.mask)
+    assert rel_l2(go.cpu().numpy(), ro) < TOL and rel_l2(gp.cpu().numpy(), rp) < TOL
+    assert abs(llk.cpu().numpy()[0] - rl) < TOL * abs(rl)
+
+
 @pytest.mark.parametrize("n,j", [(32, 21), (64, 300)])
 def test_sub_pixel_sums_against_the_oracle(n, j):
     import paper_2008_11511_amd as P
