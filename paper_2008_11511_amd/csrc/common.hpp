@@ -128,6 +128,17 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
     return (b & 7) * (full >> 3) + (b >> 3);
 }
 
+// The frame slot and first row of logical block b of a row pass whose blocks
+// hold R rows of one frame: the same rows of F consecutive slots, then the next
+// rows, so that a row of the probe is read by F neighbouring blocks.
+template <int N, int R, int F>
+__device__ __forceinline__ int2 row_block(int b, int S) {
+    constexpr int RG = N / R;
+    static_assert(N % R == 0, "a block's rows are of one frame");
+    const int c = b / (F * RG), r = b % (F * RG), fc = S - c * F < F ? S - c * F : F;
+    return make_int2(c * F + r % fc, r / fc * R);
+}
+
 // Streaming load: data read once (exit waves in the gathers) are marked
 // non-temporal so that they do not evict the data the gathers reuse from L2
 // (the probe, the object rows).

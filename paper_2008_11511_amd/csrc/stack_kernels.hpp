@@ -9,20 +9,58 @@ namespace ptycho {
 
 // ============================================================ row passes ===
 
+// Frames whose same rows neighbouring blocks of a row pass take (row_block); 0:
+// the rows of one frame after another, the frame a value of each thread.
+// What a frame of 512 points reads besides its waves - view and probe, the
+// line search's two directions too - is 4 to 8 MB per mode, more than an
+// XCD's 4 MB L2 holds from one frame to the next.  Eight frames side by side
+// read a probe row once: rows of 400 frames x 4 modes 895 -> 823 us, the line
+// search's 3203 -> 1764 us; the DM form, which streams old waves as well, is
+// best at four (1611 -> 1547 us, eight 1550-1680).  At 1024 points the gain is
+// the frame's index being one per block (scalar view and probe bases): 647 ->
+// 444 us and DM 682 -> 511 us for 100 frames, the line search 910 -> 800 us at
+// four; more frames side by side lose it again (16: 640-680 us).  At 2048 the
+// same for the plain form (526 -> 448 us), while DM and the line search are
+// slower (481 -> 536 us), as is DM at 256 (309 -> 348 us), where the probe
+// stays in the L2 anyway and the plain form gains 5%.
+template <int N, int MODE>
+__host__ __device__ constexpr int fwd_frames() {
+    if (N == 256) return MODE == IN_PHI ? 4 : 0;
+    if (N == 512) return MODE == IN_DM ? 4 : 8;
+    if (N == 1024) return MODE == IN_LS || MODE == IN_LS2 ? 4 : 1;
+    return N > 1024 && MODE == IN_PHI ? 1 : 0;
+}
+// The inverse rows gain where the probe alone is twice the L2: 512 points and
+// four modes, 1553 -> 1439 us (AP), 1693 -> 1611 us (DM); with three modes
+// 451 -> 481 us, at 1024 points up to 40% slower.
+template <int N, int K>
+__host__ __device__ constexpr int inv_frames() {
+    return N == 512 && K >= 4 ? 4 : 0;
+}
+
 // Forward row FFT of the stack's exit waves.  Block = RB consecutive rows of
-// the flattened (slot, y) row index of one probe mode (blockIdx.y); thread =
-// (row, t).  The object view is re-read per mode from the caches.
+// the flattened (slot, y) row index of one probe mode (blockIdx.y), or RB rows
+// of one frame in row_block's order; thread = (row, t).  The object view is re-read per mode from the caches.
 template <int N, int MODE, bool NF, bool SUB>
 __global__ __launch_bounds__(256) void k_rows_fwd(StackArgs a) {
     using G = RowGeom<N>;
-    constexpr int E = G::E, T = G::T, RB = G::RB;
+    constexpr int E = G::E, T = G::T, RB = G::RB, FR = fwd_frames<N, MODE>();
     __shared__ float2 lds[G::LDS_F2];
     const int tid = threadIdx.x, rr = tid / T, t = tid % T;
     const int k = blockIdx.y;
-    const int g = xcd_block(blockIdx.x, gridDim.x) * RB + rr;
-    const bool active = g < a.S * N;
-    const int gg = active ? g : a.S * N - 1;
-    const int s = gg / N, y = gg % N;
+    int s, y;
+    bool active = true;
+    if constexpr (FR > 0) {
+        const int2 b = row_block<N, RB, FR>(xcd_block(blockIdx.x, gridDim.x), a.S);
+        s = b.x;
+        y = b.y + rr;
+    } else {
+        const int g = xcd_block(blockIdx.x, gridDim.x) * RB + rr;
+        active = g < a.S * N;
+        const int gg = active ? g : a.S * N - 1;
+        s = gg / N;
+        y = gg % N;
+    }
     const int j = a.order[a.s0 + s];
     const int2 o = a.offs[j];
     const size_t orow = (size_t)(o.x + y) * a.Nx + o.y;
@@ -114,13 +152,22 @@ __global__ __launch_bounds__(256) void k_rows_fwd(StackArgs a) {
 template <int N, int K, int MODE, bool WQ, bool NF, bool SUB>
 __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a) {
     using G = InvRowGeom<N>;
-    constexpr int E = G::E, T = G::T, RQ = G::RQ;
+    constexpr int E = G::E, T = G::T, RQ = G::RQ, FR = inv_frames<N, K>();
     __shared__ float2 lds[K * RQ * G::ROW_F2];
     const int k = threadIdx.x / G::TPM, lane = threadIdx.x % G::TPM, rr = lane / T, t = lane % T;
-    const int g = xcd_block(blockIdx.x, gridDim.x) * RQ + rr;
-    const bool active = g < a.S * N;
-    const int gg = active ? g : a.S * N - 1;
-    const int s = gg / N, y = gg % N;
+    int s, y;
+    bool active = true;
+    if constexpr (FR > 0) {
+        const int2 b = row_block<N, RQ, FR>(xcd_block(blockIdx.x, gridDim.x), a.S);
+        s = b.x;
+        y = b.y + rr;
+    } else {
+        const int g = xcd_block(blockIdx.x, gridDim.x) * RQ + rr;
+        active = g < a.S * N;
+        const int gg = active ? g : a.S * N - 1;
+        s = gg / N;
+        y = gg % N;
+    }
     const int j = a.order[a.s0 + s];
     RowLds<N> L(lds, k * RQ + rr);
 
