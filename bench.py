@@ -237,9 +237,8 @@ PROFILE_SPECS = {
         "anchors": ["void ptycho::k_cols_joint<256, 3, 1, false>", "void ptycho::k_cols_seq<256, 6, false>"],
         "classes": {"rows_fwd": "void ptycho::k_rows_fwd<256, 0, false, false>",
                     "cols": "void ptycho::k_cols_joint<256, 3, 1, false>",
-                    "rows_inv": "void ptycho::k_rows_inv<256, 3, 0, true, false, false>",
+                    "rows_inv": "void ptycho::k_rows_inv_grad<256, 3, false>",
                     "gather_obj": "ptycho::k_gather_obj",
-                    "gather_probe": "void ptycho::k_gather_probe<3, true>",
                     "ls_rows": "void ptycho::k_rows_fwd<256, 4, false, false>",
                     "ls_cols": "void ptycho::k_cols_seq<256, 6, false>"}},
     "apdm512_dm_cycle": {
