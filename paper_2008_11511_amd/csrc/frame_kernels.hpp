@@ -211,6 +211,14 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs 
     constexpr int E = G::E, KS = G::KS, KG = G::KG;
     constexpr bool DM = OP == OP_CORR;
     constexpr float nrm = 1.0f / ((float)N * (float)N);
+    // Where the planes leave room for one block per CU, nothing hides a load that
+    // waits behind a transform: the observed data, the probe and the DM form's
+    // view are loaded before it (64 x 64, DM, three modes: 333 frames 55 -> 52 us,
+    // 1500 frames 163 -> 161; four modes 69 -> 65, 204 -> 200).  At 128 points
+    // and one mode, 16 waves of up to 115 registers, it gave nothing (2000
+    // frames: 288 -> 292 us DM, 218 -> 227 AP).
+    constexpr bool AHEAD = N == 64 && G::LDS_F2 * sizeof(float2) > 80 * 1024;
+    constexpr bool AHEAD_OBJ = AHEAD && DM && !SUB;
     extern __shared__ __attribute__((aligned(1024))) float2 lds_frame[];
     const FrameThread<N, K> th(a);
     float2 *plane = lds_frame + (th.f * KG + th.k) * N * N;
@@ -238,22 +246,24 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs 
         }
     };
 
+    // the data of the pixels (r, x) this thread owns
+    float iobv[E], sc[E];
+    auto pixel = [&](int e) { return (unsigned)(th.r * N + th.tr) + elem_const<N, E, LastRadix<N, E, -1>::value>(e); };
+    auto load_iobs = [&] {
+        const float *io = a.iobs + (size_t)th.j * n2;
+#pragma unroll
+        for (int e = 0; e < E; ++e) iobv[e] = io[pixel(e)];
+    };
     float2 u[KS][E];
 #pragma unroll
     for (int m = 0; m < KS; ++m) {
         form(u[m], th.k + m);
+        if constexpr (AHEAD) load_iobs();
         frame_forward<N>(u[m], C, th.t, R, th.tr);
     }
-
-    // the data of the pixels (r, x) this thread owns, then intensity -> scale
-    float iobv[E], sc[E];
-    auto pixel = [&](int e) { return (unsigned)(th.r * N + th.tr) + elem_const<N, E, LastRadix<N, E, -1>::value>(e); };
-    {
-        const float *io = a.iobs + (size_t)th.j * n2;
-#pragma unroll
-        for (int e = 0; e < E; ++e) iobv[e] = io[pixel(e)];
-    }
+    if constexpr (!AHEAD) load_iobs();
     const unsigned bad_bits = mask_bits<E>(a.mask, pixel);
+    // intensity -> scale
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         sc[e] = 0.0f;
@@ -309,18 +319,30 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs 
         const int k = th.k + m;
 #pragma unroll
         for (int e = 0; e < E; ++e) u[m][e] = cscale(u[m][e], sc[e]);
+        const float2 *p = a.probe + k * n2;
+        float2 pv[AHEAD ? E : 1], ov[AHEAD_OBJ ? E : 1];
+        if constexpr (AHEAD) {
+            const int t = opaque_t<N>(th.t);
+            const unsigned c = opaque(th.c);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int y = out_index<N, E, +1>(t, e);
+                pv[e] = (p + y * N)[c];
+                if constexpr (AHEAD_OBJ) ov[e] = frame_view<SUB>(a, a.obj, th.o, fr, y, c);
+            }
+        }
         frame_inverse<N>(u[m], C, th.t, R, th.tr);
         const int t = opaque_t<N>(th.t);
         const unsigned c = opaque(th.c);
-        const float2 *p = a.probe + k * n2;
         float2 *ps = a.psi_out + ((size_t)th.j * K + k) * n2;
         float2 *scr = a.scr + ((size_t)th.s * K + k) * n2;
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int y = out_index<N, E, +1>(t, e);
-            const float2 pe = (p + y * N)[c];
+            const float2 pe = AHEAD ? pv[AHEAD ? e : 0] : (p + y * N)[c];
             float2 w = u[m][e];
-            if constexpr (DM) w = cadd(cmul(frame_view<SUB>(a, a.obj, th.o, fr, y, c), pe), w);
+            if constexpr (AHEAD_OBJ) w = cadd(cmul(ov[e], pe), w);
+            else if constexpr (DM) w = cadd(cmul(frame_view<SUB>(a, a.obj, th.o, fr, y, c), pe), w);
             if (th.active) {
                 if constexpr (OP == OP_GRAD) scr[scr_at<N>(y, c)] = w;
                 else if (a.psi_out != nullptr) st_stream(ps + y * N + c, w);
