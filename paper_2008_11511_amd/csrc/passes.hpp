@@ -126,8 +126,9 @@ static bool grad_rows(const ptycho_plan_s *p, const StackArgs &a) {
 }
 template <int N, int K, bool NF>
 static void launch_rows_inv_grad(ptycho_plan_s *p, const StackArgs &a, int chunks, hipStream_t s) {
-    const dim3 grid((unsigned)(N / InvRowGeom<N>::RQ * chunks)), block(InvRowGeom<N>::TPM * K);
-    hipLaunchKernelGGL((k_rows_inv_grad<N, K, NF>), grid, block, 0, s, a, chunks, p->pnum, p->pden);
+    const int blocks = std::max(1, std::min(p->L.gblocks, chunks));
+    const dim3 grid((unsigned)(N / InvRowGeom<N>::RQ * blocks)), block(InvRowGeom<N>::TPM * K);
+    hipLaunchKernelGGL((k_rows_inv_grad<N, K, NF>), grid, block, 0, s, a, blocks, chunks, p->pnum, p->pden);
 }
 
 // One pass over all stacks: forward rows, column op, inverse rows and the

@@ -56,7 +56,7 @@ struct Layout {
         off_numP, off_denP, off_pnum, off_pden, off_part, off_red, off_scal, off_s2, off_bsum, off_prop,
         off_pspart, off_shift, off_pos, off_pos0, off_frac, off_bmax, off_cpart, total;
     int pos_chunks;               // row chunks per frame of the position-shift sums
-    int gchunks;                  // frame chunks of the gradient's inverse row pass
+    int gblocks, gchunks;         // blocks per row group and frame chunks of the gradient's inverse row pass
 };
 
 // Per-kernel-class timing with HIP events on the plan's stream.

@@ -109,13 +109,13 @@ static int probe_chunks(const ptycho_desc_t &d) {
     return (int)std::min<long>(c, d.n_frames);
 }
 
-// Frame chunks of the gradient's inverse row pass (k_rows_inv_grad), of at
-// least two frames each.  Its registers allow 8 wavefronts per CU: up to 512
+// Blocks per row group of the gradient's inverse row pass (k_rows_inv_grad), of
+// at least two frames each.  Its registers allow 8 wavefronts per CU: up to 512
 // points the blocks are one round of that (256 x 3 modes, 500 frames: 326 us
 // in one round, 443 in one and a third, 336 in two, 352 in six).  Larger
 // frames leave a block so many rows and so few frames that unequal blocks
 // count: six rounds (1024 x 1, 100 frames: 838 us in one round, 684 in six).
-static int grad_chunks(const ptycho_desc_t &d) {
+static int grad_blocks(const ptycho_desc_t &d) {
     if (d.n < 128) return 0;
     const int T = d.n / row_e(d.n), tpm = std::max(64, T);
     const long resident = 256L * (8 / (tpm / 64 * d.n_modes)), rows = (long)d.n / (tpm / T);
@@ -180,8 +180,12 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.nred = std::max({(size_t)L.nstacks * L.maxb, (size_t)L.nstacks_ls * L.maxb_ls * 2,
                        (size_t)L.nstacks_ls2 * L.maxb_ls2 * 2});
     L.pchunks = probe_chunks(d);
-    L.gchunks = grad_chunks(d);
-    const size_t nchunks = std::max(L.pchunks, L.gchunks);
+    // a chunk of the gradient's sums is never longer than one of the probe
+    // gather's: a chunk is one running sum in 32 bits, whose error grows with
+    // its frames
+    L.gblocks = grad_blocks(d);
+    L.gchunks = std::max(L.pchunks, L.gblocks);
+    const size_t nchunks = L.gchunks;
     L.pos_chunks = N / pos_rows(N);
     const size_t n2 = (size_t)N * N, no = (size_t)d.obj_ny * d.obj_nx;
     size_t o = 0;

@@ -256,10 +256,13 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
 }
 
 // Inverse row FFT of the gradient pass with both sums taken from the gradient
-// waves in registers: a block walks the frames of one chunk (blockIdx / row
-// groups) on the same RQ rows, writes each frame's q as above, and keeps the
-// chunk's probe numerators sum_j conj(O_j) psi_jk and denominators sum_j |O_j|^2
-// of its rows, which k_probe_reduce adds over the chunks.  Integer windows.
+// waves in registers: a block walks the frames of its consecutive chunks
+// (C blocks per row group, M chunks in all, M >= C) on the same RQ rows, writes
+// each frame's q as above, and keeps a chunk's probe numerators
+// sum_j conj(O_j) psi_jk and denominators sum_j |O_j|^2 of its rows, which
+// k_probe_reduce adds over the chunks.  Integer windows.
+// M is separate from C so that a chunk, a running sum in 32 bits, is as short
+// as the sums need while the blocks are as many as the chip takes.
 // Bound by memory; it reads K and writes one complex frame where k_rows_inv
 // also wrote the K waves back and k_gather_probe read them again: 500 frames
 // of 256^2 x 3 modes took 347 + 152 us and take 326, 400 of 512^2 x 4 1552 +
@@ -270,8 +273,8 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
 // 506 us), except at 2048 points, where the probe and view rows no longer stay
 // in the L2 from one frame to the next (20 frames: 586 against 732).
 template <int N, int K, bool NF>
-__global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv_grad(StackArgs a, int C, float2 *pnum,
-                                                                         float *pden) {
+__global__ __launch_bounds__(InvRowGeom<N>::TPM * K, 2) void k_rows_inv_grad(StackArgs a, int C, int M,
+                                                                         float2 *pnum, float *pden) {
     using G = InvRowGeom<N>;
     constexpr int E = G::E, T = G::T, RQ = G::RQ, RG = N / RQ;
     static_assert(N % RQ == 0, "a block's rows are of one frame");
@@ -279,78 +282,82 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv_grad(StackA
     __shared__ float2 lds[K * RQ * G::ROW_F2];
     const int k = threadIdx.x / G::TPM, lane = threadIdx.x % G::TPM, rr = lane / T, t = lane % T;
     const int b = xcd_block(blockIdx.x, gridDim.x), c = b / RG, y = b % RG * RQ + rr;
-    const int s0 = (int)((long)c * a.S / C), s1 = (int)((long)(c + 1) * a.S / C);
+    const int m0 = (int)((long)c * M / C), m1 = (int)((long)(c + 1) * M / C);
     RowLds<N> L(lds, k * RQ + rr);
     const float2 *prow = a.probe + ((size_t)k * N + y) * N;
-    float2 acc[E];
-    float den[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        acc[e] = make_float2(0.0f, 0.0f);
-        den[e] = 0.0f;
-    }
-    for (int s = s0; s < s1; ++s) {
-        const int2 o = a.offs[a.order[a.s0 + s]];
-        const float2 *src = a.scr + ((size_t)s * K + k) * N * N;
-        const float2 *orow = a.obj + ((size_t)(o.x + y) * a.Nx + o.y);
-        const int tf = opaque(t);
-        float2 u[E], ov[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-            u[e] = ld_stream(src + scr_at<N>(y, NF ? in_index<N, E, -1>(tf, e) : in_index<N, E, +1>(tf, e)));
-        if constexpr (EARLY) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) ov[e] = orow[out_index<N, E, +1>(tf, e)];
-        }
-        if constexpr (NF) {
-            fft1d<N, E, -1>(u, tf, L);
-            const float2 *qx = a.prop + N;
-#pragma unroll
-            for (int e = 0; e < E; ++e) u[e] = cmulc(qx[out_index<N, E, -1>(tf, e)], u[e]);
-        }
-        const int t1 = NF ? opaque(tf) : tf;
-        fft1d<N, E, +1>(u, t1, L);
-        if constexpr (!EARLY) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) ov[e] = orow[out_index<N, E, +1>(t1, e)];
-        }
+    const size_t n2 = (size_t)N * N;
+    for (int m = m0; m < m1; ++m) {
+        const int s0 = (int)((long)m * a.S / M), s1 = (int)((long)(m + 1) * a.S / M);
+        float2 acc[E];
+        float den[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const float2 cv = cmulc(ov[e], u[e]);
-            acc[e] = cadd(acc[e], cv);
-            if (e % K == k) den[e] += cnorm(ov[e]);
-            u[e] = cmulc(prow[out_index<N, E, +1>(t1, e)], u[e]);
+            acc[e] = make_float2(0.0f, 0.0f);
+            den[e] = 0.0f;
         }
-        float2 *qrow = a.qbuf + ((size_t)s * N + y) * N;
-        if constexpr (K == 1) {
+        for (int s = s0; s < s1; ++s) {
+            const int2 o = a.offs[a.order[a.s0 + s]];
+            const float2 *src = a.scr + ((size_t)s * K + k) * N * N;
+            const float2 *orow = a.obj + ((size_t)(o.x + y) * a.Nx + o.y);
+            const int tf = opaque(t);
+            float2 u[E], ov[E];
 #pragma unroll
-            for (int e = 0; e < E; ++e) st_stream(qrow + out_index<N, E, +1>(t1, e), u[e]);
-        } else {
-            __syncthreads();             // the transforms' LDS reads are done
+            for (int e = 0; e < E; ++e)
+                u[e] = ld_stream(src + scr_at<N>(y, NF ? in_index<N, E, -1>(tf, e) : in_index<N, E, +1>(tf, e)));
+            if constexpr (EARLY) {
 #pragma unroll
-            for (int e = 0; e < E; ++e) L.st(out_index<N, E, +1>(t1, e), u[e]);
-            __syncthreads();
+                for (int e = 0; e < E; ++e) ov[e] = orow[out_index<N, E, +1>(tf, e)];
+            }
+            if constexpr (NF) {
+                fft1d<N, E, -1>(u, tf, L);
+                const float2 *qx = a.prop + N;
+#pragma unroll
+                for (int e = 0; e < E; ++e) u[e] = cmulc(qx[out_index<N, E, -1>(tf, e)], u[e]);
+            }
+            const int t1 = NF ? opaque(tf) : tf;
+            fft1d<N, E, +1>(u, t1, L);
+            if constexpr (!EARLY) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) ov[e] = orow[out_index<N, E, +1>(t1, e)];
+            }
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                if (e % K != k) continue;
-                const int x = out_index<N, E, +1>(t1, e);
-                float2 q = RowLds<N>(lds, rr).ld(x);
+                const float2 cv = cmulc(ov[e], u[e]);
+                acc[e] = cadd(acc[e], cv);
+                if (e % K == k) den[e] += cnorm(ov[e]);
+                u[e] = cmulc(prow[out_index<N, E, +1>(t1, e)], u[e]);
+            }
+            float2 *qrow = a.qbuf + ((size_t)s * N + y) * N;
+            if constexpr (K == 1) {
 #pragma unroll
-                for (int m = 1; m < K; ++m) q = cadd(q, RowLds<N>(lds, m * RQ + rr).ld(x));
-                st_stream(qrow + x, q);
+                for (int e = 0; e < E; ++e) st_stream(qrow + out_index<N, E, +1>(t1, e), u[e]);
+            } else {
+                __syncthreads();             // the transforms' LDS reads are done
+#pragma unroll
+                for (int e = 0; e < E; ++e) L.st(out_index<N, E, +1>(t1, e), u[e]);
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    if (e % K != k) continue;
+                    const int x = out_index<N, E, +1>(t1, e);
+                    float2 q = RowLds<N>(lds, rr).ld(x);
+#pragma unroll
+                    for (int h = 1; h < K; ++h) q = cadd(q, RowLds<N>(lds, h * RQ + rr).ld(x));
+                    st_stream(qrow + x, q);
+                }
             }
         }
-    }
-    const size_t n2 = (size_t)N * N;
-    float2 *pn = pnum + ((size_t)c * K + k) * n2 + (size_t)y * N;
-    float *pd = pden + (size_t)c * n2 + (size_t)y * N;
+        float2 *pn = pnum + ((size_t)m * K + k) * n2 + (size_t)y * N;
+        float *pd = pden + (size_t)m * n2 + (size_t)y * N;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int x = out_index<N, E, +1>(t, e);
-        pn[x] = acc[e];
-        if (e % K == k) pd[x] = den[e];
+        for (int e = 0; e < E; ++e) {
+            const int x = out_index<N, E, +1>(t, e);
+            pn[x] = acc[e];
+            if (e % K == k) pd[x] = den[e];
+        }
     }
 }
+
 // ========================================================== column pass ===
 // OP_CORR writes (s - 1) F(X) instead of s F(X): since P_F(X) = X + F^-1((s-1) F(X))
 // (s = 1 at bad pixels), the DM update Psi + P_F(2 Phi - Psi) - Phi equals
