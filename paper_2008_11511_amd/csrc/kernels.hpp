@@ -743,6 +743,10 @@ __global__ __launch_bounds__(256) void k_obj_chunk_reduce(const int *rtile, cons
     }
 }
 
+// Groups of chunks that k_probe_reduce adds side by side: four where there are
+// many chunks.
+__host__ __device__ constexpr int probe_groups(int chunks) { return chunks >= 8 ? 4 : 1; }
+
 // Probe numerator/denominator over the frames order[q0 .. q0+nq), with the
 // given object: one thread per probe pixel, all K modes (the object value of
 // a frame is read once for the K modes); the range is split into gridDim.z
@@ -750,8 +754,12 @@ __global__ __launch_bounds__(256) void k_obj_chunk_reduce(const int *rtile, cons
 // are read from the stack scratch by slot (FROM_SCR, slot = q - q0) or from
 // stored exit waves [J][K][N][N] by frame.  The order is the plan's
 // spatially compact one, so object rows are reused in L2.
+// From the scratch (the gradient) the chunks are those of k_rows_inv_grad, so
+// that both ways of taking the sums give the same bits; one block then takes
+// one chunk or, of large frames, all of them, added as k_probe_reduce would.
 struct ProbeAllArgs {
     int N, K, q0, nq, Nx, Ny;
+    int chunks;          // chunks of the range (FROM_SCR; else gridDim.z)
     const float2 *frac;  // sub-pixel windows [J], or null
     int lw;             // log2 of the exit waves' tile width (log2 N: row-major)
     const int2 *offs;
@@ -771,31 +779,62 @@ __global__ __launch_bounds__(256) void k_gather_probe(ProbeAllArgs a) {
     const int y = idx / N, x = idx % N;
     const size_t fsz = (size_t)N * N;
     const size_t vpix = tiled_at(y, x, N, a.lw);
-    const int j0 = (int)((long)c * a.nq / C), j1 = (int)((long)(c + 1) * a.nq / C);
     float2 acc[K];
+    float den;
+    // the sums over frames [j0, j1) of the range, in acc and den
+    auto run = [&](int j0, int j1) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] = make_float2(0.0f, 0.0f);
-    float den = 0.0f;
-    // the next frame's table entries are read a frame ahead of its data
-    int jn = j0 < j1 ? a.order[a.q0 + j0] : 0;
-    int2 on = a.offs[jn];
-    for (int q = j0; q < j1; ++q) {
-        const int j = jn;
-        const int2 o = on;
-        if (q + 1 < j1) {
-            jn = a.order[a.q0 + q + 1];
-            on = a.offs[jn];
-        }
-        const float2 ov = a.frac != nullptr ? view_at(a.obj, view_row(a.Ny, a.Nx, o, a.frac[j], y), x)
-                                            : a.obj[(size_t)(o.x + y) * a.Nx + o.y + x];
-        const float2 *ps = a.psi + (size_t)(FROM_SCR ? q : j) * K * fsz + vpix;
+        for (int k = 0; k < K; ++k) acc[k] = make_float2(0.0f, 0.0f);
+        den = 0.0f;
+        // the next frame's table entries are read a frame ahead of its data
+        int jn = j0 < j1 ? a.order[a.q0 + j0] : 0;
+        int2 on = a.offs[jn];
+        for (int q = j0; q < j1; ++q) {
+            const int j = jn;
+            const int2 o = on;
+            if (q + 1 < j1) {
+                jn = a.order[a.q0 + q + 1];
+                on = a.offs[jn];
+            }
+            const float2 ov = a.frac != nullptr ? view_at(a.obj, view_row(a.Ny, a.Nx, o, a.frac[j], y), x)
+                                                : a.obj[(size_t)(o.x + y) * a.Nx + o.y + x];
+            const float2 *ps = a.psi + (size_t)(FROM_SCR ? q : j) * K * fsz + vpix;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const float2 cv = cmulc(ov, ld_stream(ps + k * fsz));
-            acc[k].x += cv.x;
-            acc[k].y += cv.y;
+            for (int k = 0; k < K; ++k) {
+                const float2 cv = cmulc(ov, ld_stream(ps + k * fsz));
+                acc[k].x += cv.x;
+                acc[k].y += cv.y;
+            }
+            den += cnorm(ov);
         }
-        den += cnorm(ov);
+    };
+    const int M = FROM_SCR ? a.chunks : C;
+    if (!FROM_SCR || M == C) {
+        run((int)((long)c * a.nq / M), (int)((long)(c + 1) * a.nq / M));
+    } else {
+        // all chunks (C == 1), in the groups of k_probe_reduce
+        const int G = probe_groups(M);
+        float2 sum[K], grp[K];
+        float dsum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < K; ++k) sum[k] = make_float2(0.0f, 0.0f);
+        for (int g = 0; g < G; ++g) {
+            float dgrp = 0.0f;
+#pragma unroll
+            for (int k = 0; k < K; ++k) grp[k] = make_float2(0.0f, 0.0f);
+            for (int m = g * M / G; m < (g + 1) * M / G; ++m) {
+                run((int)((long)m * a.nq / M), (int)((long)(m + 1) * a.nq / M));
+#pragma unroll
+                for (int k = 0; k < K; ++k) grp[k] = cadd(grp[k], acc[k]);
+                dgrp += den;
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) sum[k] = cadd(sum[k], grp[k]);
+            dsum += dgrp;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[k] = sum[k];
+        den = dsum;
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) a.part_num[((size_t)c * K + k) * fsz + idx] = acc[k];

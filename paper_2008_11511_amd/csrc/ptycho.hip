@@ -180,9 +180,9 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.nred = std::max({(size_t)L.nstacks * L.maxb, (size_t)L.nstacks_ls * L.maxb_ls * 2,
                        (size_t)L.nstacks_ls2 * L.maxb_ls2 * 2});
     L.pchunks = probe_chunks(d);
-    // a chunk of the gradient's sums is never longer than one of the probe
-    // gather's: a chunk is one running sum in 32 bits, whose error grows with
-    // its frames
+    // a chunk of the gradient's sums, whichever kernel takes them, is never
+    // longer than one of the probe gather's: a chunk is one running sum in 32
+    // bits, whose error grows with its frames
     L.gblocks = grad_blocks(d);
     L.gchunks = std::max(L.pchunks, L.gblocks);
     const size_t nchunks = L.gchunks;
@@ -797,7 +797,11 @@ int ptycho::probe_sums(ptycho_plan_s *p, const float *obj, const float2 *psi, in
     a.part_num = p->pnum;
     a.part_den = p->pden;
     const long n2 = (long)a.N * a.N;
-    const int chunks = std::max(1, std::min(p->L.pchunks, nq));
+    a.chunks = std::max(1, std::min(from_scr ? p->L.gchunks : p->L.pchunks, nq));
+    // the gradient's chunks (see k_gather_probe): a block each up to 512 points;
+    // from 1024 one block takes them all, where a block per chunk would write
+    // and read again up to twelve partials of a probe's size
+    const int chunks = from_scr && a.N >= 1024 ? 1 : a.chunks;
     dim3 grid((unsigned)((n2 + 255) / 256), 1, chunks);
     Timed tm(p, from_scr ? TC_GATHER_PROBE : TC_PROBE_ALL);
     with_k(a.K, [&](auto kk) {
@@ -814,8 +818,7 @@ int ptycho::probe_sums(ptycho_plan_s *p, const float *obj, const float2 *psi, in
 int ptycho::reduce_probe(ptycho_plan_s *p, int chunks, bool accumulate) {
     const int K = p->d.n_modes;
     const long n2 = (long)p->d.n * p->d.n;
-    // chunk groups side by side where there are many chunks of few values
-    const int G = chunks >= 8 ? 4 : 1;
+    const int G = probe_groups(chunks);
     p->npartP = (int)std::max(1L, std::min((n2 * K * G + 255) / 256, (long)NPART));
     if (G == 4)
         hipLaunchKernelGGL((k_probe_reduce<4>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,

@@ -1,5 +1,6 @@
 """How the gradient's probe sums are split: the running sums in 32 bits are as
-short as the probe gather's."""
+short as the probe gather's, and plans on integer windows and on positions
+whose corners are integers add the same chunks in the same order."""
 import numpy as np
 import pytest
 
@@ -43,3 +44,35 @@ def test_probe_gradient_runs_are_no_longer_than_the_gather_s(n, k, j, chunks):
         run = run + term
     rms = lambda s, m: float(np.sqrt(np.mean((s / (m * term.astype(np.float64)) - 1.0) ** 2)))  # noqa: E731
     assert rms(got, j) < 1.5 * rms(run, length)
+
+
+@pytest.mark.parametrize("n,k,j,stack", [(128, 3, 30, 0),       # fewer frames than chunks, two frames a block
+                                         (128, 1, 67, 0), (128, 2, 140, 0), (128, 3, 16, 0), (128, 3, 41, 20),
+                                         (256, 1, 40, 0), (256, 3, 16, 0), (512, 1, 16, 0), (512, 4, 9, 0),
+                                         (1024, 1, 26, 0),      # four groups of three chunks
+                                         (1024, 2, 13, 7), (2048, 1, 7, 0)])
+def test_integer_positions_give_the_integer_plan_s_gradient_bitwise(n, k, j, stack):
+    """The probe's gradient and the LLK at every size; up to 16 frames, where no object tile's frames are split into
+    chunks (a positions plan counts frames that may move onto a tile, so its chunks begin elsewhere), all of it."""
+    import paper_2008_11511_amd as P
+    dev = device()
+    shape = (n + 45, n + 61)
+    obj, probe, iobs = problem(n, k, j, shape, n * k + j, dev)
+    offs = np.random.default_rng(j).integers(2, 40, (j, 2)).astype(np.int32)
+    pos = offs + n / 2.0 - np.array(shape) / 2.0
+    both = P.UPDATE_OBJECT | P.UPDATE_PROBE
+    a = P.Plan(offs, iobs, None, k, shape, stack=stack)
+    b = P.Plan.with_positions(pos, iobs, None, k, shape, max_shift=1.0, stack=stack)
+
+    def outputs(plan, update):
+        print(f"[gpu-case] sum order n={n} k={k} j={j} stack={stack} update={update}", flush=True)
+        g_o, g_p, llk = plan.ml_grad(obj, probe)
+        o, p, st = obj.clone(), probe.clone(), plan.ml_state()
+        plan.ml_cycle(o, p, st, 1, update, reset=True)
+        return [x.cpu().numpy() for x in ((g_p, llk, g_o, o, p) if j <= 16 else (g_p, llk))]
+
+    ref = outputs(a, both)
+    # the last call moves b's positions after its cycle, so it comes last
+    for update in (both, both | P.UPDATE_POSITIONS):
+        for x, y in zip(ref, outputs(b, update)):
+            np.testing.assert_array_equal(x, y)
