@@ -180,12 +180,17 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.nred = std::max({(size_t)L.nstacks * L.maxb, (size_t)L.nstacks_ls * L.maxb_ls * 2,
                        (size_t)L.nstacks_ls2 * L.maxb_ls2 * 2});
     L.pchunks = probe_chunks(d);
-    // a chunk of the gradient's sums, whichever kernel takes them, is never
-    // longer than one of the probe gather's: a chunk is one running sum in 32
-    // bits, whose error grows with its frames
+    // a chunk of the gradient's sums, whichever kernel takes them, has at most
+    // eight frames or is no longer than one of the probe gather's: a chunk is one
+    // running sum in 32 bits, whose error grows with its frames; the blocks of
+    // the row pass take the same number of chunks each
     L.gblocks = grad_blocks(d);
-    L.gchunks = std::max(L.pchunks, L.gblocks);
-    const size_t nchunks = L.gchunks;
+    L.gchunks = L.pchunks;
+    if (L.gblocks > 0) {
+        const int need = std::min(L.pchunks, (J + 7) / 8);
+        L.gchunks = (need + L.gblocks - 1) / L.gblocks * L.gblocks;
+    }
+    const size_t nchunks = std::max(L.pchunks, L.gchunks);
     L.pos_chunks = N / pos_rows(N);
     const size_t n2 = (size_t)N * N, no = (size_t)d.obj_ny * d.obj_nx;
     size_t o = 0;
