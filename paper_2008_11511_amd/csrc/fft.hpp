@@ -54,19 +54,30 @@ __device__ __forceinline__ constexpr float2 root16() {
     return float2{C[M], DIR < 0 ? -C[4 - M] : C[4 - M]};
 }
 
-// (a, b) <- (a + w b, a - w b) in six operations: the sum takes two fused
-// multiply-adds per component, the difference is 2 a minus the sum.  (Product
-// first and then sum and difference are eight; each result here has as many
-// roundings or one less.)  A twiddled radix-16 pass takes about 220 vector
-// instructions this way instead of 284, a radix-8 pass 84 instead of 108, and
-// holds fewer registers (512-point columns of 4 modes: 200 -> 156): 17 x
-// 2048^2 near-field DM cycle 1.99 -> 1.93 ms, 800 x 512^2 x 4-mode AP cycle
-// 11.54 -> 11.27 ms, 150 x 512^2 x 2-mode intensities 0.364 -> 0.331 ms.
+// (a, b) <- (a + w b, a - w b): each of the four results by two fused
+// multiply-adds of its own, so that a difference is rounded at its own size: the
+// eight operations of product, sum and difference, and one rounding less each.
+// Taken as 2 a minus the sum, the difference costs two operations less (1% of
+// a far-field projection cycle, 2 to 5% of a ML cycle) but carries the sum's
+// rounding, the larger one where the difference is weak: the rms error over the
+// weaker half of an exit wave's field, against a transform that multiplies by
+// the twiddles first, is then 1.10 to 1.18 at 64 to 512 points, and 0.94 to 0.98
+// this way.
 __device__ __forceinline__ void bfly(float2 &a, float2 &b, float2 w) {
-    const float sx = __builtin_fmaf(-w.y, b.y, __builtin_fmaf(w.x, b.x, a.x));
-    const float sy = __builtin_fmaf(w.y, b.x, __builtin_fmaf(w.x, b.y, a.y));
-    b = make_float2(__builtin_fmaf(2.0f, a.x, -sx), __builtin_fmaf(2.0f, a.y, -sy));
-    a = make_float2(sx, sy);
+    const float2 p = a, q = b;
+    a = make_float2(__builtin_fmaf(-w.y, q.y, __builtin_fmaf(w.x, q.x, p.x)),
+                    __builtin_fmaf(w.y, q.x, __builtin_fmaf(w.x, q.y, p.y)));
+    b = make_float2(__builtin_fmaf(w.y, q.y, __builtin_fmaf(-w.x, q.x, p.x)),
+                    __builtin_fmaf(-w.y, q.x, __builtin_fmaf(-w.x, q.y, p.y)));
+}
+// The same for w = exp(DIR i pi / 4), whose parts are alike: the sum and the
+// difference of b's parts first, six operations.
+template <int DIR>
+__device__ __forceinline__ void bfly_eighth(float2 &a, float2 &b) {
+    constexpr float c = 0.70710678118654752f;
+    const float2 p = a, q = cadd(b, rot90<DIR>(b));
+    a = make_float2(__builtin_fmaf(c, q.x, p.x), __builtin_fmaf(c, q.y, p.y));
+    b = make_float2(__builtin_fmaf(-c, q.x, p.x), __builtin_fmaf(-c, q.y, p.y));
 }
 // The same for w = 1.
 __device__ __forceinline__ void bfly1(float2 &a, float2 &b) {
@@ -105,6 +116,9 @@ struct Dft {
             if constexpr (K == 0) {
                 bfly1(e[K], o[K]);
                 bfly1(e[K + R / 4], t);
+            } else if constexpr (K * 8 == R) {
+                bfly_eighth<DIR>(e[K], o[K]);
+                bfly_eighth<DIR>(e[K + R / 4], t);
             } else {
                 constexpr float2 w = root16<K * (16 / R), DIR>();
                 bfly(e[K], o[K], w);

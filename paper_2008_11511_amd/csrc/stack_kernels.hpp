@@ -273,7 +273,7 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
 // 506 us), except at 2048 points, where the probe and view rows no longer stay
 // in the L2 from one frame to the next (20 frames: 586 against 732).
 template <int N, int K, bool NF>
-__global__ __launch_bounds__(InvRowGeom<N>::TPM * K, 2) void k_rows_inv_grad(StackArgs a, int C, int M,
+__global__ __launch_bounds__(InvRowGeom<N>::TPM * K) __attribute__((amdgpu_waves_per_eu(2, N < 2048 ? 2 : 8))) void k_rows_inv_grad(StackArgs a, int C, int M,
                                                                          float2 *pnum, float *pden) {
     using G = InvRowGeom<N>;
     constexpr int E = G::E, T = G::T, RQ = G::RQ, RG = N / RQ;
@@ -367,11 +367,15 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K, 2) void k_rows_inv_grad(Sta
 // Exchange buffers of the read-only column pass: the line search's three
 // transforms of a mode run pass by pass together while their buffers fit
 // 96 KiB of LDS, one after the other through one buffer beyond that.
-template <int N, int OP>
+template <int N, int OP, bool NF = false>
 struct ColSeqBufs {
     static constexpr int SETS = (OP == OP_LS || OP == OP_LS2) ? 3 : 1;
     using G = ColGeom<N, seq_cb(N, SETS == 3)>;
     static constexpr int value = ((size_t)SETS * ColGeom<N>::LDS_F2 * 8 <= 96 * 1024) ? SETS : 1;
+    // waves per SIMD: the far-field LLK and intensities need 81 to 85 registers,
+    // one to five too many for six waves, and fit 80 with at most one spilled
+    // (LLK of 60 frames of 512^2 x 2 modes 172 -> 163 us)
+    static constexpr int MIN_WAVES = !NF && SETS == 1 && N >= 128 && N <= 512 && (N != 256 || OP == OP_LLK) ? 6 : 1;
 };
 
 // Waves per SIMD a column kernel is compiled for: up to 3 modes the DM and
@@ -380,12 +384,18 @@ struct ColSeqBufs {
 // 512-thread blocks instead of one at 512 points, 3 modes: AP columns of 150
 // frames 533 -> 362 us); the 256-point, 3-mode projection would spill 56 bytes
 // and is faster at 3 waves (299 against 364 us, 500 frames).  The near-field
-// pass at 2048 points with one mode gets 4 waves too.  The others keep the
-// compiler's choice.
+// pass at 2048 points with one mode gets 4 waves too, the 256-point, 4-mode
+// projection 3 (two registers spilled; 170 registers would leave it 2: columns
+// of a 100-frame AP cycle of 191 us 24 us slower).  The others are held to two
+// waves: left alone, the compiler gives the 256-thread blocks of the 2048-point
+// pass with three and four modes more than 256 registers, one wave per SIMD (AP
+// cycle of 17 near-field frames, 4 modes: 6.44 ms, 5.01 held to two waves and 5.69
+// in whole tiles).
 template <int N, int K, int OP, bool NF>
 struct ColMinWaves {
     static constexpr int value = ((!NF && ColJoint<N, K>::SEQ && N <= 512 && K <= 3 && (N == 512 || OP != OP_PROJECT)) ||
-                                  (NF && N >= 2048 && K == 1)) ? 4 : 1;
+                                  (NF && N >= 2048 && K == 1)) ? 4
+                                 : (!NF && N == 256 && K == 4 && OP == OP_PROJECT) ? 3 : 2;
 };
 
 // Row (y) index of register e of thread t at the detector-plane step: after
@@ -534,7 +544,7 @@ __global__ __launch_bounds__((ColJoint<N, K>::G::THREADS), (ColMinWaves<N, K, OP
 // transforms' inputs are read once, non-temporally (line search at 500 x
 // 256^2 x 3 modes: ML cycle 2.34 -> 2.31 ms).
 template <int N, int OP, bool NF>
-__global__ __launch_bounds__((ColSeqBufs<N, OP>::G::THREADS)) void k_cols_seq(StackArgs a) {
+__global__ __launch_bounds__((ColSeqBufs<N, OP>::G::THREADS), (ColSeqBufs<N, OP, NF>::MIN_WAVES)) void k_cols_seq(StackArgs a) {
     using G = typename ColSeqBufs<N, OP>::G;
     constexpr int E = G::E, CB = G::CB;
     extern __shared__ float2 lds_dyn[];
