@@ -847,7 +847,7 @@ __global__ __launch_bounds__(256) void k_gather_probe(ProbeAllArgs a) {
 // receives the maximum of the block's denominators.  (One thread per value
 // walking all chunks, one load at a time, took 20 us for 4096 values in 32
 // chunks; 5 us this way.)
-template <int G>
+template <int G, int U>
 __global__ __launch_bounds__(256) void k_probe_reduce(const float2 *part_num, const float *part_den, int C, int K,
                                                       long n2, float2 *numP, float *denP, int accumulate,
                                                       float *part) {
@@ -864,17 +864,17 @@ __global__ __launch_bounds__(256) void k_probe_reduce(const float2 *part_num, co
         float2 s = make_float2(0.0f, 0.0f);
         float d = 0.0f;
         const long ic = in ? i : 0, id = dn ? i : 0;
-        for (int c = c0; c < c1; c += 4) {
-            float2 v[4];
-            float w[4];
+        for (int c = c0; c < c1; c += U) {
+            float2 v[U];
+            float w[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 const int cc = min(c + u, c1 - 1);
                 v[u] = part_num[(size_t)cc * np + ic];
                 w[u] = dn ? part_den[(size_t)cc * n2 + id] : 0.0f;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 if (c + u >= c1) break;
                 s = cadd(s, v[u]);
                 d += w[u];

@@ -825,12 +825,15 @@ int ptycho::reduce_probe(ptycho_plan_s *p, int chunks, bool accumulate) {
     const long n2 = (long)p->d.n * p->d.n;
     const int G = probe_groups(chunks);
     p->npartP = (int)std::max(1L, std::min((n2 * K * G + 255) / 256, (long)NPART));
-    if (G == 4)
-        hipLaunchKernelGGL((k_probe_reduce<4>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
-                           K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
-    else
-        hipLaunchKernelGGL((k_probe_reduce<1>), dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks,
-                           K, n2, p->numP, p->denP, accumulate ? 1 : 0, p->part + NPART);
+    // one chunk (large frames) is one load per value: the four loads in flight
+    // would be the same one four times
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(p->npartP), dim3(256), 0, p->stream, p->pnum, p->pden, chunks, K, n2, p->numP,
+                           p->denP, accumulate ? 1 : 0, p->part + NPART);
+    };
+    if (G == 4) launch(k_probe_reduce<4, 4>);
+    else if (chunks > 1) launch(k_probe_reduce<1, 4>);
+    else launch(k_probe_reduce<1, 1>);
     LAUNCHCHK();
     return PTYCHO_OK;
 }
