@@ -131,8 +131,8 @@ __device__ __forceinline__ int xcd_block(int b, int nb) {
 // The frame slot and first row of logical block b of a row pass whose blocks
 // hold R rows of one frame: the same rows of F consecutive slots, then the next
 // rows, so that a row of the probe is read by F neighbouring blocks.
-template <int N, int R, int F>
-__device__ __forceinline__ int2 row_block(int b, int S) {
+template <int N, int R>
+__device__ __forceinline__ int2 row_block(int b, int S, int F) {
     constexpr int RG = N / R;
     static_assert(N % R == 0, "a block's rows are of one frame");
     const int c = b / (F * RG), r = b % (F * RG), fc = S - c * F < F ? S - c * F : F;
@@ -228,6 +228,7 @@ struct StackArgs {
     double *red;                 // per-block partial sums of this launch
     float eps;
     int llk_model;               // noise model of OP_LLK (LlkModel)
+    int side;                    // frames side by side in the forward rows (see fwd_frames)
 };
 
 

@@ -48,7 +48,8 @@ static void launch_cols_seq(const StackArgs &a, hipStream_t s) {
 // Forward row pass of input form MODE: the sub-pixel-window instance when the
 // plan's windows interpolate, the integer one otherwise.
 template <int N, int MODE, bool NF>
-static void launch_rows_fwd(const StackArgs &a, dim3 grid, hipStream_t s) {
+static void launch_rows_fwd(StackArgs a, dim3 grid, hipStream_t s) {
+    a.side = side_frames<N, MODE, NF>(a.S, a.K);
     if (a.frac != nullptr) hipLaunchKernelGGL((k_rows_fwd<N, MODE, NF, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_rows_fwd<N, MODE, NF, false>), grid, dim3(256), 0, s, a);
 }

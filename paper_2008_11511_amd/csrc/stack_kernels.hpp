@@ -13,26 +13,41 @@ namespace ptycho {
 // the rows of one frame after another, the frame a value of each thread.
 // What a frame of 512 points reads besides its waves - view and probe, the
 // line search's two directions too - is 4 to 8 MB per mode, more than an
-// XCD's 4 MB L2 holds from one frame to the next.  Eight frames side by side
+// XCD's 4 MB L2 holds from one frame to the next, and eight frames side by side
 // read a probe row once: rows of 400 frames x 4 modes 895 -> 823 us, the line
 // search's 3203 -> 1764 us; the DM form, which streams old waves as well, is
-// best at four (1611 -> 1547 us, eight 1550-1680).  At 1024 points the gain is
-// the frame's index being one per block (scalar view and probe bases): 647 ->
-// 444 us and DM 682 -> 511 us for 100 frames, the line search 910 -> 800 us at
-// four; more frames side by side lose it again (16: 640-680 us).  At 2048 the
-// same for the plain form (526 -> 448 us), while DM and the line search are
-// slower (481 -> 536 us), as is DM at 256 (309 -> 348 us), where the probe
-// stays in the L2 anyway and the plain form gains 5%.
-template <int N, int MODE>
+// best at four (1611 -> 1547 us, eight 1550-1680).  But a stack that the eight
+// L2s hold together (32 MB) is read by the column pass from the L2 that its
+// rows were written to, and only if an XCD's blocks are of few whole frames:
+// intensities of 4 frames x 4 modes took 24.6 us in the frames' order and 28.5
+// side by side, 8 frames x 1 mode 15.4 and 18.9; of 8 frames x 4 modes (64 MB)
+// 42.8 and 37.0.  So side_frames() gives 1 up to there.
+// At 256 and 1024 points, and at 2048 in the plain form, the gain is the frame's
+// index being one per block (scalar view and probe bases), in the frames' order:
+// intensities of 256 frames of 256^2 x 4 modes 228 -> 222 us, of 64 frames of
+// 1024^2 x 1 628 -> 472 us, of 4 frames of 2048^2 x 4 574 -> 512 us.  The DM
+// form loses by it at 256 (256 frames x 4 modes 825 -> 844 us a cycle) and 2048
+// points.  The line search at 1024 points gains by four frames side by side in
+// the near field (17 frames x 4 modes 2412 -> 1578 us) and where the third
+// transform is kept (16 frames x 4 modes 2591 -> 2469 us a ML cycle), but loses
+// where the far field forms all three (32 frames x 2 modes: 1306 us in the
+// frames' order, 1742 side by side, 1385 with a scalar index alone).
+template <int N, int MODE, bool NF>
 __host__ __device__ constexpr int fwd_frames() {
-    if (N == 256) return MODE == IN_PHI ? 4 : 0;
+    if (N == 256) return MODE == IN_PHI ? 1 : 0;
     if (N == 512) return MODE == IN_DM ? 4 : 8;
-    if (N == 1024) return MODE == IN_LS || MODE == IN_LS2 ? 4 : 1;
+    if (N == 1024) return MODE == IN_LS ? (NF ? 4 : 0) : MODE == IN_LS2 ? 4 : 1;
     return N > 1024 && MODE == IN_PHI ? 1 : 0;
 }
-// The inverse rows gain where the probe alone is twice the L2: 512 points and
-// four modes, 1553 -> 1439 us (AP), 1693 -> 1611 us (DM); with three modes
-// 451 -> 481 us, at 1024 points up to 40% slower.
+// The frames side by side of a launch of S frames x K modes, up to fwd_frames.
+template <int N, int MODE, bool NF>
+static int side_frames(int S, int K) {
+    const size_t bytes = sizeof(float2) * S * K * N * N;
+    return N == 512 && MODE == IN_PHI && bytes <= (size_t(32) << 20) ? 1 : fwd_frames<N, MODE, NF>();
+}
+// Measured to gain at 512 points with four modes only: 1553 -> 1439 us (AP, 400
+// frames), 1693 -> 1611 us (DM); with three modes 451 -> 481 us, at 1024 points,
+// whatever the modes, up to 40% slower.
 template <int N, int K>
 __host__ __device__ constexpr int inv_frames() {
     return N == 512 && K >= 4 ? 4 : 0;
@@ -44,14 +59,14 @@ __host__ __device__ constexpr int inv_frames() {
 template <int N, int MODE, bool NF, bool SUB>
 __global__ __launch_bounds__(256) void k_rows_fwd(StackArgs a) {
     using G = RowGeom<N>;
-    constexpr int E = G::E, T = G::T, RB = G::RB, FR = fwd_frames<N, MODE>();
+    constexpr int E = G::E, T = G::T, RB = G::RB, FR = fwd_frames<N, MODE, NF>();
     __shared__ float2 lds[G::LDS_F2];
     const int tid = threadIdx.x, rr = tid / T, t = tid % T;
     const int k = blockIdx.y;
     int s, y;
     bool active = true;
     if constexpr (FR > 0) {
-        const int2 b = row_block<N, RB, FR>(xcd_block(blockIdx.x, gridDim.x), a.S);
+        const int2 b = row_block<N, RB>(xcd_block(blockIdx.x, gridDim.x), a.S, FR > 1 ? a.side : 1);
         s = b.x;
         y = b.y + rr;
     } else {
@@ -158,7 +173,7 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
     int s, y;
     bool active = true;
     if constexpr (FR > 0) {
-        const int2 b = row_block<N, RQ, FR>(xcd_block(blockIdx.x, gridDim.x), a.S);
+        const int2 b = row_block<N, RQ>(xcd_block(blockIdx.x, gridDim.x), a.S, FR);
         s = b.x;
         y = b.y + rr;
     } else {
