@@ -92,6 +92,38 @@ static bool by_frame(const ptycho_plan_s *p, const float2 *keep) {
     return (N <= 64 && K == 1) || p->L.S >= 128;
 }
 
+// Whether a read-only pass takes a frame per block.  At 32 points and up to two
+// modes at 64 it is the faster way at any count, but for a line search of one
+// frame, whose three transforms it does one after the other (32^2 x 1 mode 21
+// against 13 us, 64^2 x 4 modes 49 against 20).  At 64 points, three and four
+// modes leave room for one block per CU, so the time goes up by a whole round
+// with every 256 frames; a round has to be 0.7 full (intensities, 4 modes, us,
+// frame per block / three passes: 12 / 9.6 at 16 frames, 12 / 16 at 200, 24 / 21
+// at 300, 24 / 26 at 400, 69 / 83 at 1500), and sub-pixel views of two modes
+// follow them (10.2 / 9.5 at 32 frames, 11 / 14 at 200).  The likelihood's
+// logarithms, which such a block takes with nothing else in flight, turn it from
+// the fourth round on (3 modes: 17 / 20 at 200, 42 / 41 at 768, 82 / 75 at 1500).
+// Sub-pixel views of four modes at 32 points: 10.5 / 9.6 at 64 frames, 10.6 / 12.5
+// at 200.  The line search of four modes spills 100 registers, that of
+// sub-pixel views pays for four values a pixel in each of its three transforms:
+// they are the faster way only while they save launches, from 3 frames on in
+// the first round and in a full second one (4 modes: 50 / 40 us at 2 frames,
+// 50 / 77 at 4, 65 / 100 at 256, 112 / 78 at 300, 116 / 120 at 400, 172 / 122 at
+// 600, 348 / 266 at 1500).
+template <int N, int K, int OP, bool SUB>
+static bool read_by_frame(int J) {
+    const int rounds = (J + 255) / 256;
+    const bool full = 10L * J >= 7L * 256 * rounds;
+    if (OP == OP_LS) {
+        if (J == 1) return false;
+        if (N == 64 && (K == 4 || (SUB && K >= 2)))
+            return rounds == 1 ? (K < 4 || J > 2) : rounds == 2 && full;
+        return true;
+    }
+    if (N == 32) return !(SUB && K == 4) || J > 128;
+    return K <= (SUB ? 1 : 2) || (full && (OP != OP_LLK || K == 2 || rounds <= 3));
+}
+
 template <int N, int K>
 static dim3 frame_blocks(int sn) {
     return dim3((unsigned)((sn + FrameGeom<N, K>::FPB - 1) / FrameGeom<N, K>::FPB));
@@ -293,18 +325,26 @@ static int forward_pass_n(ptycho_plan_s *p, int op, const float *obj, const floa
     return with_nf(p, [&](auto nf) {
         constexpr bool NF = decltype(nf)::value;
         if constexpr (has_frame_read<N>() && !NF) {
-            switch (op) {
-                case OP_LLK: return frame_pass_op<N, OP_LLK>(p, obj, probe, dobj, dprobe, icalc, llk_model);
-                case OP_ICALC: return frame_pass_op<N, OP_ICALC>(p, obj, probe, dobj, dprobe, icalc, llk_model);
-                case OP_LS: return frame_pass_op<N, OP_LS>(p, obj, probe, dobj, dprobe, icalc, llk_model);
-                case OP_LS2:
-                    // the gradient pass of the same plan kept no row transforms
-                    if (with_k(p->d.n_modes, [&](auto kk) { return (int)by_frame<N, decltype(kk)::value>(p, keep); }))
-                        return frame_pass_op<N, OP_LS>(p, obj, probe, dobj, dprobe, icalc, llk_model);
-                    return forward_pass_op<N, OP_LS2, NF>(p, obj, probe, dobj, dprobe, icalc, llk_model, keep);
-                default: return fail(PTYCHO_E_INVALID, "internal: unknown forward op");
-            }
-        } else
+            // the gradient pass of a plan whose projections take a frame per block
+            // kept no row transforms
+            if (op == OP_LS2 &&
+                with_k(p->d.n_modes, [&](auto kk) { return (int)by_frame<N, decltype(kk)::value>(p, keep); }))
+                op = OP_LS;
+            const auto whole = [&](auto o) {
+                constexpr int OP = decltype(o)::value;
+                const int J = p->d.n_frames;
+                return with_k(p->d.n_modes, [&](auto kk) {
+                    constexpr int K = decltype(kk)::value;
+                    return (int)(p->pos_ready ? read_by_frame<N, K, OP, true>(J) : read_by_frame<N, K, OP, false>(J));
+                }) != 0;
+            };
+            if (op == OP_LLK && whole(std::integral_constant<int, OP_LLK>()))
+                return frame_pass_op<N, OP_LLK>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+            if (op == OP_ICALC && whole(std::integral_constant<int, OP_ICALC>()))
+                return frame_pass_op<N, OP_ICALC>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+            if (op == OP_LS && whole(std::integral_constant<int, OP_LS>()))
+                return frame_pass_op<N, OP_LS>(p, obj, probe, dobj, dprobe, icalc, llk_model);
+        }
         switch (op) {
             case OP_LLK: return forward_pass_op<N, OP_LLK, NF>(p, obj, probe, dobj, dprobe, icalc, llk_model, keep);
             case OP_ICALC: return forward_pass_op<N, OP_ICALC, NF>(p, obj, probe, dobj, dprobe, icalc, llk_model, keep);
