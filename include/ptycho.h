@@ -424,7 +424,9 @@ PTYCHO_API int ptycho_fft2(int32_t n, int32_t count, float *data_dev, int32_t di
  * 0 stops recording.  PTYCHO_E_INVALID for bits beyond class 7.
  * Small far-field frames whose three passes run as one kernel count it as
  * class 2 (projections) or class 1 (read-only passes); the other passes then
- * record empty intervals.
+ * record empty intervals.  Where the ML gradient's inverse rows take the
+ * probe sums themselves (integer windows from 128 points), class 2 includes
+ * them and class 4 is the reduction of their partial sums alone.
  * ptycho_plan_timing_read waits for the last recorded event and returns the
  * summed milliseconds and the launch count of one class since timing was
  * last enabled. */

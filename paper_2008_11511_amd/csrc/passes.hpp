@@ -242,8 +242,10 @@ static int project_pass_nk(ptycho_plan_s *p, const float *obj, const float *prob
         // ML position shifts from the gradient wave left in the scratch
         if (kind == 2 && p->shifts_in_grad) st = launch_ml_shifts(p, obj, probe, s0, sn);
         if (!st && (acc & ACC_OBJ)) st = object_sums(p, sidx);
-        if (!st && probe_done) st = reduce_probe(p, chunks, sidx > 0);
-        else if (!st && (acc & ACC_PROBE)) st = probe_sums(p, obj, p->scr, s0, sn, true, sidx > 0);
+        if (!st && probe_done) {
+            Timed tm(p, TC_GATHER_PROBE);
+            st = reduce_probe(p, chunks, sidx > 0);
+        } else if (!st && (acc & ACC_PROBE)) st = probe_sums(p, obj, p->scr, s0, sn, true, sidx > 0);
         if (st) return st;
     }
     return PTYCHO_OK;
