@@ -1207,6 +1207,7 @@ extern "C" int ptycho_icalc(ptycho_plan_t p, const float *obj, const float *prob
     int st = check_prop_ptrs(p, obj, probe);
     if (st) return st;
     if (!icalc) return fail(PTYCHO_E_INVALID, "null icalc output");
+    begin_call(p);
     return forward_pass(p, OP_ICALC, obj, probe, nullptr, nullptr, icalc);
 }
 
@@ -1259,9 +1260,11 @@ extern "C" int ptycho_ml_linesearch(ptycho_plan_t p, const float *obj, const flo
 
 // ------------------------------------------------------------ CG ML cycle --
 // State of the CG iteration: scalars, direction and previous gradient of the
-// object and probe, inner-product partials, and the forward row transforms
-// of every frame at the current point (kept by the gradient pass for the
-// line search, which then forms only its two other transforms).
+// object and probe, 8 KB that nothing reads (a saved state keeps its layout;
+// the inner-product partials once held there lie in the workspace), and the
+// forward row transforms of every frame at the current point (kept by the
+// gradient pass for the line search, which then forms only its two other
+// transforms).
 static size_t ml_state_bytes(const ptycho_desc_t &d) {
     const size_t no = (size_t)d.obj_ny * d.obj_nx, np = (size_t)d.n_modes * d.n * d.n;
     return up(sizeof(double) * CG_NSCAL) + 2 * up(sizeof(float2) * no) + 2 * up(sizeof(float2) * np) +
