@@ -43,8 +43,10 @@ constexpr int col_cb(int n) {
 // no room for a second block on the CU, half a tile per 256-thread block does:
 // the blocks' barriers and memory phases then overlap.  512 points, 4 modes
 // (156 registers): columns of 800 frames 4.08 -> 2.87 ms; line search at 512
-// points (173 registers): 400 frames of 4 modes 2.49 -> 2.05 ms; 2048 points: 20
-// far-field frames 564 -> 449 us, 17 near-field ones 605 -> 568 us.  With up to 3 modes at 512 points, in the other read-only
+// points (173 registers): 400 frames of 4 modes 2.49 -> 2.11 ms; 2048 points: 20
+// far-field frames 564 -> 480 us, 17 near-field ones 672 -> 590 us, and with four
+// modes, both sides held to two waves per SIMD, AP cycles of 17 near-field frames
+// 5.65 -> 5.01 ms.  With up to 3 modes at 512 points, in the other read-only
 // passes and at 1024 points two whole-tile blocks fit, and reading full 64-byte
 // rows is faster (512, 2 modes: 348 against 381 us; intensities 149 / 227).
 constexpr int joint_cb(int n, int k) { return (n == 512 && k >= 4) ? 4 : n >= 2048 ? 2 : col_cb(n); }

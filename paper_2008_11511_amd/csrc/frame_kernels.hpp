@@ -203,7 +203,10 @@ __device__ __forceinline__ float2 frame_view(const StackArgs &a, const float2 *b
 }
 
 // One frame: exit waves (IN_PHI) or 2 Phi - Psi (OP_CORR), the Fourier step,
-// and back.  New exit waves go to psi_out when it is given (AP, DM) or to the
+// and back.  At 128 points with two modes the kernel sits at the 128 registers
+// that a 1024-thread block may hold and spills 41 to 55 more, a seventh of its
+// time (500 frames, AP: 109 us, 90 with butterflies that need 20 registers less
+// and round worse).  New exit waves go to psi_out when it is given (AP, DM) or to the
 // stack scratch (OP_GRAD); q = sum_k conj(P_k) Psi_k to qbuf when it is given.
 template <int N, int K, int OP, bool SUB>
 __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs a) {
@@ -387,7 +390,10 @@ __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame(StackArgs 
 // search's two coefficients (A = P O, B = P dO + dP O, C = dP dO of each mode,
 // one transform after the other).  The modes are side by side in a block as
 // above; their intensities and first- and second-order terms are summed
-// through the planes.
+// through the planes.  The line search keeps three sums and two waves, 112
+// values, beside the transform: at 64 points it spills 12 registers with three
+// modes (168 of its own) and 103 to 106 with four (128), which is why it then
+// takes three passes at most counts (see read_by_frame).
 template <int N, int K, int OP, bool SUB>
 __global__ __launch_bounds__((FrameGeom<N, K>::THREADS)) void k_frame_read(StackArgs a) {
     using G = FrameGeom<N, K>;

@@ -280,15 +280,19 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
 // as the sums need while the blocks are as many as the chip takes.
 // Bound by memory; it reads K and writes one complex frame where k_rows_inv
 // also wrote the K waves back and k_gather_probe read them again: 500 frames
-// of 256^2 x 3 modes took 347 + 152 us and take 326, 400 of 512^2 x 4 1552 +
-// 601 and take 1543, 1000 of 128^2 x 4 353 + 102 and take 235.  The sums cost
-// 170-230 registers, two waves per SIMD; held to three, the spills cost more
-// than the third wave gives (256^2 x 3: 493 us).  The view is loaded after
-// the transform, which the registers then need not hold (512 x 1: 430 against
-// 506 us), except at 2048 points, where the probe and view rows no longer stay
-// in the L2 from one frame to the next (20 frames: 586 against 732).
+// of 256^2 x 3 modes took 347 + 152 us and take 331, 400 of 512^2 x 4 1552 +
+// 601 and take 1690, 1000 of 128^2 x 4 353 + 102 and take 238.  The sums cost
+// 200-255 registers, two waves per SIMD; held to three, the spills cost more
+// than the third wave gives (256^2 x 3: 493 us).  With one mode the compiler
+// would reach for three by itself and load less at a time: 17 near-field frames
+// of 512^2 55 us, 36 when held to two, 17 of 1024^2 209 and 186; with more
+// modes, or at 2048 points, the hint makes the code worse (512^2 x 4: 1758).
+// The view is loaded after the transform, which the registers then need not
+// hold (512 x 1: 430 against 506 us), except at 2048 points, where the probe and
+// view rows no longer stay in the L2 from one frame to the next (20 frames: 586
+// against 732).
 template <int N, int K, bool NF>
-__global__ __launch_bounds__(InvRowGeom<N>::TPM * K) __attribute__((amdgpu_waves_per_eu(2, N < 2048 ? 2 : 8))) void k_rows_inv_grad(StackArgs a, int C, int M,
+__global__ __launch_bounds__(InvRowGeom<N>::TPM * K) __attribute__((amdgpu_waves_per_eu(2, N < 2048 && K == 1 ? 2 : 8))) void k_rows_inv_grad(StackArgs a, int C, int M,
                                                                          float2 *pnum, float *pden) {
     using G = InvRowGeom<N>;
     constexpr int E = G::E, T = G::T, RQ = G::RQ, RG = N / RQ;
