@@ -292,8 +292,9 @@ __global__ __launch_bounds__(InvRowGeom<N>::TPM * K) void k_rows_inv(StackArgs a
 // view rows no longer stay in the L2 from one frame to the next (20 frames: 586
 // against 732).
 template <int N, int K, bool NF>
-__global__ __launch_bounds__(InvRowGeom<N>::TPM * K) __attribute__((amdgpu_waves_per_eu(2, N < 2048 && K == 1 ? 2 : 8))) void k_rows_inv_grad(StackArgs a, int C, int M,
-                                                                         float2 *pnum, float *pden) {
+__global__ __launch_bounds__(InvRowGeom<N>::TPM * K)
+__attribute__((amdgpu_waves_per_eu(2, N < 2048 && K == 1 ? 2 : 8)))
+void k_rows_inv_grad(StackArgs a, int C, int M, float2 *pnum, float *pden) {
     using G = InvRowGeom<N>;
     constexpr int E = G::E, T = G::T, RQ = G::RQ, RG = N / RQ;
     static_assert(N % RQ == 0, "a block's rows are of one frame");
@@ -563,7 +564,8 @@ __global__ __launch_bounds__((ColJoint<N, K>::G::THREADS), (ColMinWaves<N, K, OP
 // transforms' inputs are read once, non-temporally (line search at 500 x
 // 256^2 x 3 modes: ML cycle 2.34 -> 2.31 ms).
 template <int N, int OP, bool NF>
-__global__ __launch_bounds__((ColSeqBufs<N, OP>::G::THREADS), (ColSeqBufs<N, OP, NF>::MIN_WAVES)) void k_cols_seq(StackArgs a) {
+__global__ __launch_bounds__((ColSeqBufs<N, OP>::G::THREADS), (ColSeqBufs<N, OP, NF>::MIN_WAVES))
+void k_cols_seq(StackArgs a) {
     using G = typename ColSeqBufs<N, OP>::G;
     constexpr int E = G::E, CB = G::CB;
     extern __shared__ float2 lds_dyn[];
