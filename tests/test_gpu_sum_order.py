@@ -4,6 +4,9 @@ whose corners are integers add the same chunks in the same order."""
 import numpy as np
 import pytest
 
+import oracle
+from cases import make_problem, rel_l2, small
+
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
@@ -76,3 +79,18 @@ def test_integer_positions_give_the_integer_plan_s_gradient_bitwise(n, k, j, sta
     for update in (both, both | P.UPDATE_POSITIONS):
         for x, y in zip(ref, outputs(b, update)):
             np.testing.assert_array_equal(x, y)
+
+
+def test_gradient_of_several_hundred_frames_matches_the_oracle():
+    """Chunks of 19 frames, two to a block."""
+    import paper_2008_11511_amd as P
+    dev = device()
+    print("[gpu-case] long chunks n=256 k=3 j=304", flush=True)
+    pb = make_problem(small("ml256", n=256, k=3, j=304, obj=(420, 433), step=4.0, mask_frac=0.03), start="ml")
+    to = lambda a, t: torch.from_numpy(np.ascontiguousarray(a)).to(dev, t)  # noqa: E731
+    plan = P.Plan(pb.offsets, to(pb.iobs, torch.float32), to(pb.mask, torch.uint8), 3, pb.wl.obj_shape)
+    go, gp, llk = plan.ml_grad(to(pb.obj0, torch.complex64), to(pb.probe0, torch.complex64))
+    ro, rp, rl = oracle.ml_grad(pb.obj0, pb.probe0, pb.offsets, pb.iobs, pb.mask)
+    # relative L2, as in the parity tests
+    assert rel_l2(go.cpu().numpy(), ro) < 1e-4 and rel_l2(gp.cpu().numpy(), rp) < 1e-4
+    assert abs(llk.cpu().numpy()[0] - rl) < 1e-4 * abs(rl)
