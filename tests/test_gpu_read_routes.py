@@ -12,13 +12,13 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-4          # relative, as in the parity tests
 
 
-def on_device(pb, pos=None):
+def on_device(pb, pos=None, stack=0):
     import paper_2008_11511_amd as P
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     to = lambda a, t: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0", t)  # noqa: E731
     args = to(pb.iobs, torch.float32), to(pb.mask, torch.uint8), pb.wl.n_modes, pb.wl.obj_shape
-    plan = P.Plan(pb.offsets, *args) if pos is None else P.Plan.with_positions(pos, *args)
+    plan = P.Plan(pb.offsets, *args, stack=stack) if pos is None else P.Plan.with_positions(pos, *args, stack=stack)
     return plan, to(pb.obj0, torch.complex64), to(pb.probe0, torch.complex64), to
 
 
@@ -37,13 +37,14 @@ def check(pb, plan, o, p, to, frac=None):
     assert abs(c[0] - r[0]) < TOL * abs(r[0]) and abs(c[1] - r[1]) < TOL * abs(r[1])
 
 
-@pytest.mark.parametrize("n,k,j", [(32, 1, 1), (32, 4, 2), (64, 4, 2), (64, 4, 3), (64, 3, 179), (64, 3, 180),
-                                   (64, 4, 257), (64, 4, 359), (64, 3, 769)])
-def test_integer_windows(n, k, j):
-    print(f"[gpu-case] read routes n={n} k={k} j={j}", flush=True)
+@pytest.mark.parametrize("n,k,j,stack", [(32, 1, 1, 0), (32, 4, 2, 0), (64, 4, 2, 0), (64, 4, 3, 0), (64, 3, 179, 0),
+                                         (64, 3, 180, 0), (64, 4, 257, 0), (64, 4, 359, 0), (64, 3, 769, 0),
+                                         (64, 3, 150, 40), (64, 4, 300, 255), (64, 4, 300, 256)])
+def test_integer_windows(n, k, j, stack):
+    print(f"[gpu-case] read routes n={n} k={k} j={j} stack={stack}", flush=True)
     shape = (2 * n + 5, 2 * n + 1)
     pb = make_problem(small("dm256", n=n, k=k, j=j, obj=shape, step=0.4 * n / np.sqrt(j), mask_frac=0.03), start="ml")
-    check(pb, *on_device(pb))
+    check(pb, *on_device(pb, stack=stack))
 
 
 @pytest.mark.parametrize("n,k,j", [(32, 4, 128), (32, 4, 129), (64, 2, 1), (64, 2, 179), (64, 2, 180), (64, 2, 257)])
