@@ -187,7 +187,7 @@ static Layout layout_for(const ptycho_desc_t &d) {
     L.gblocks = grad_blocks(d);
     L.gchunks = L.pchunks;
     if (L.gblocks > 0) {
-        const int need = std::min(L.pchunks, (J + 7) / 8);
+        const int need = std::min(L.pchunks, (L.S + 7) / 8);       // frames are summed stack by stack
         L.gchunks = (need + L.gblocks - 1) / L.gblocks * L.gblocks;
     }
     const size_t nchunks = std::max(L.pchunks, L.gchunks);
