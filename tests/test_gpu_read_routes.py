@@ -65,3 +65,17 @@ def test_forward_rows_around_the_cached_stack_size(k, j):
     plan, o, p, _ = on_device(pb)
     got = plan.icalc(o, p).cpu().numpy()
     assert rel_l2(got, oracle.simulate_intensity(pb.obj0, pb.probe0, pb.offsets)) < TOL
+
+
+def test_a_cycle_whose_line_search_takes_three_passes():
+    """A plan whose projections take a frame per block keeps no row transforms: the line search forms all three."""
+    import paper_2008_11511_amd as P
+    n, k, j = 64, 4, 300
+    print(f"[gpu-case] CG cycle n={n} k={k} j={j}", flush=True)
+    pb = make_problem(small("dm256", n=n, k=k, j=j, obj=(2 * n + 5, 2 * n + 1), step=0.4 * n / np.sqrt(j),
+                            mask_frac=0.03), start="ml")
+    plan, o, p, _ = on_device(pb)
+    both = oracle.UPDATE_OBJECT | oracle.UPDATE_PROBE
+    plan.ml_cycle(o, p, plan.ml_state(), 1, P.UPDATE_OBJECT | P.UPDATE_PROBE, reset=True)
+    ro, rp = oracle.ml_cycle(pb.obj0, pb.probe0, oracle.CGState(), pb.offsets, pb.iobs, pb.mask, both)
+    assert rel_l2(o.cpu().numpy(), ro) < TOL and rel_l2(p.cpu().numpy(), rp) < TOL
